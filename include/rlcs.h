@@ -134,9 +134,8 @@ rlcs_status rlcs_retrace(const void* r, const void* q, const void* eq, const voi
  *   mu       [N, T] behaviour-policy probability of the taken action, dtype (nonzero)
  *   bv, boot E_pi Q of the true successor of a truncated step / of s_T, as for rlcs_retrace
  *   delta, q_ret  as for rlcs_retrace
- *   A        number of actions, A >= 1. Each workgroup stages its chunk's [steps, A] slices
- *            of q and pi in LDS: whole for A <= 28, in slices of the action axis otherwise
- *            (32 actions at a time: one 128-byte line of float32, half a line of bfloat16).
+ *   A        number of actions, A >= 1. Any A and any element alignment of q and pi run on the
+ *            same path: groups of lanes read a step's actions four to a lane.
  *   ws       optional, at least 64 bytes, 64-byte aligned, zero-filled by the caller: the int32
  *            at byte 8 becomes 2 when a call meets an out-of-range action, and stays so until
  *            the caller clears it. Unused otherwise; NULL = no report.

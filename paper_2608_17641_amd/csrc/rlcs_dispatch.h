@@ -53,17 +53,6 @@ template <class Op> struct OneWaveRows : std::false_type {};
 template <> struct OneWaveRows<GaeOp> : std::true_type {};
 template <bool D, bool S> struct OneWaveRows<ForwardOp<D, S>> : std::true_type {};
 
-// Staged policies (full-form Retrace) use 4 waves when a 4-wave chunk's slices fit in 64 KB of
-// LDS, else 2 waves when two 2-wave workgroups fit in a CU's 160 KB (80 KB each; 4096 x 256 x 18
-// fp32 49.6 -> 48.5 us against one wave), else 1 wave.
-constexpr int kStagedWaves = 1;
-constexpr int kStagedMidWaves = 2;
-constexpr int64_t kStagedLdsBudget = 64 * 1024;
-constexpr int64_t kStagedMidLdsBudget = 80 * 1024;
-// LDS of a sliced chunk (long action axes, one wave): room for slices of one whole 128-byte line
-// of float32 actions (two slabs of 257 x 32 elements, 65.8 KB), two workgroups per CU.
-constexpr int64_t kSlicedLdsBudget = 80 * 1024;
-
 // Steps per lane: one 16-byte vector of each input.
 template <typename DT> struct Width;
 template <> struct Width<float> { static constexpr int K = 4; };
@@ -81,10 +70,6 @@ constexpr int64_t kSplitBelowRows = 256;
 // Split rows use 4-wave tiles, or 16-wave tiles when a row would have more than this many
 // 4-wave ones (all tiles of a row draw their tickets from one word).
 constexpr int64_t kMaxSmallTilesPerRow = 64;
-
-// Largest action axis of full-form Retrace whose chunk's whole [steps, A] slices are staged in
-// LDS; longer axes are staged in slices of sliced_width actions.
-constexpr int64_t kMaxActions = 28;
 
 // Longest supported row (the kernels keep offsets within a row range in 32 bits).
 constexpr int64_t kMaxT = int64_t(1) << 30;
@@ -120,7 +105,6 @@ struct Plan {
     int64_t tiles_per_row;  // tiles kernel: tiles of each row (grid = N * tiles_per_row)
     int64_t rows_per_wg;  // rows kernel: rows per workgroup
     int wave_local;       // rows kernel: no carry crosses waves
-    size_t lds_bytes;     // dynamic LDS (staged policies)
     bool pad;             // rows kernel, vector path: lanes outside the range or in row gaps skip
     int wave_rows_log2T;  // >= 0: wave_rows_kernel (rows tile a wave exactly; T = 2^log2T)
     int flat_R;           // > 0: flat_rows_kernel with this many whole rows per workgroup
@@ -132,22 +116,20 @@ template <class Op, typename DT, bool VEC, bool TR, int W, bool PAD = false>
 void launch_w(const Args& a, const Plan& p, hipStream_t stream) {
     constexpr int K = Width<DT>::K;
     const dim3 block(W * kWave);
-    if constexpr (Op::kStaged == 0) {
-        if (p.split) {
-            hipLaunchKernelGGL((tiles_kernel<Op, DT, K, W, VEC, TR>),
-                               dim3(unsigned(a.N * p.tiles_per_row)), block, 0, stream, a,
-                               p.tiles_per_row);
-            return;
-        }
+    if (p.split) {
+        hipLaunchKernelGGL((tiles_kernel<Op, DT, K, W, VEC, TR>),
+                           dim3(unsigned(a.N * p.tiles_per_row)), block, 0, stream, a,
+                           p.tiles_per_row);
+        return;
     }
     const int64_t groups = (a.N + p.rows_per_wg - 1) / p.rows_per_wg;
     hipLaunchKernelGGL((rows_kernel<Op, DT, K, W, VEC, TR, PAD>), dim3(unsigned(groups)), block,
-                       p.lds_bytes, stream, a, p.rows_per_wg, p.wave_local);
+                       0, stream, a, p.rows_per_wg, p.wave_local);
 }
 
 template <class Op, typename DT, bool VEC, bool TR>
 rlcs_status launch(const Args& a, const Plan& p, hipStream_t stream) {
-    if constexpr (VEC && Op::kStaged == 0) {
+    if constexpr (VEC) {
         if (p.flat_R > 0) {
             const dim3 grid(unsigned((a.N + p.flat_R - 1) / p.flat_R));
             if constexpr (sizeof(DT) == 4) {
@@ -177,72 +159,22 @@ rlcs_status launch(const Args& a, const Plan& p, hipStream_t stream) {
             return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
         }
     }
-    if constexpr (VEC && Op::kStaged == 0) {
+    if constexpr (VEC) {
         if (p.pad && !p.split) {
             if (p.waves == kSmallWaves) launch_w<Op, DT, true, TR, kSmallWaves, true>(a, p, stream);
             else launch_w<Op, DT, true, TR, kLargeWaves, true>(a, p, stream);
             return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
         }
     }
-    if constexpr (Op::kStaged > 0 && Op::kSliced) {
-        launch_w<Op, DT, VEC, TR, kStagedWaves>(a, p, stream);
-    } else if constexpr (Op::kStaged > 0) {
-        if (p.waves == kStagedWaves) launch_w<Op, DT, VEC, TR, kStagedWaves>(a, p, stream);
-        else if (p.waves == kStagedMidWaves) launch_w<Op, DT, VEC, TR, kStagedMidWaves>(a, p, stream);
-        else launch_w<Op, DT, VEC, TR, kSmallWaves>(a, p, stream);
-    } else {
-        if constexpr (OneWaveRows<Op>::value) {
-            if (p.waves == 1) {
-                launch_w<Op, DT, VEC, TR, 1>(a, p, stream);
-                return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
-            }
+    if constexpr (OneWaveRows<Op>::value) {
+        if (p.waves == 1) {
+            launch_w<Op, DT, VEC, TR, 1>(a, p, stream);
+            return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
         }
-        if (p.waves == kSmallWaves) launch_w<Op, DT, VEC, TR, kSmallWaves>(a, p, stream);
-        else launch_w<Op, DT, VEC, TR, kLargeWaves>(a, p, stream);
     }
+    if (p.waves == kSmallWaves) launch_w<Op, DT, VEC, TR, kSmallWaves>(a, p, stream);
+    else launch_w<Op, DT, VEC, TR, kLargeWaves>(a, p, stream);
     return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
-}
-
-// LDS bytes of a staged policy's chunk with W waves: the larger of the two [steps, A] slices and
-// the staged slots, which reuse the slices' bytes once they are reduced.
-template <class Op, typename DT>
-constexpr int64_t staged_lds_bytes(int W, int64_t A) {
-    const int64_t E = int64_t(W) * kWave * Width<DT>::K;
-    const int64_t per_block = 16 / int64_t(sizeof(DT));
-    const int64_t cap = ((E + 1) * A + 3 * per_block) / per_block * per_block;  // see stage_chunk
-    const int64_t slots = int64_t(sizeof(float)) * Op::kStaged * (E + 4);
-    const int64_t slices = 2 * cap * int64_t(sizeof(DT));
-    return slots > slices ? slots : slices;
-}
-
-// Sliced staging (long action axes), W waves: LDS elements of one array's slab of As actions
-// (SlicedStager::cap), the widest slice (a multiple of 16 bytes of DT) whose two slabs fit in
-// `budget` bytes, and the LDS bytes of a chunk (slabs or slots, which overlay them).
-template <typename DT>
-constexpr int64_t sliced_cap(int W, int64_t As) {
-    const int64_t E = int64_t(W) * kWave * Width<DT>::K, per_block = 16 / int64_t(sizeof(DT));
-    return ((E + 1) * As + per_block - 1) / per_block * per_block;
-}
-template <typename DT>
-constexpr int64_t sliced_width(int W, int64_t budget) {
-    // whole 128-byte lines of actions when one fits: a slice that ends inside a line leaves the
-    // rest of that line to the next slice, which fetched it again from HBM (float32, A = 64 and
-    // 256: 1.96 and 1.99 times the algorithmic bytes with 28-action slices)
-    const int64_t per_line = 128 / int64_t(sizeof(DT));
-    int64_t As = 0;
-    while (2 * sliced_cap<DT>(W, As + per_line) * int64_t(sizeof(DT)) <= budget) As += per_line;
-    if (As > 0) return As;
-    const int64_t per_block = 16 / int64_t(sizeof(DT));
-    As = per_block;
-    while (2 * sliced_cap<DT>(W, As + per_block) * int64_t(sizeof(DT)) <= budget) As += per_block;
-    return As;
-}
-template <class Op, typename DT>
-constexpr int64_t sliced_lds_bytes(int W, int64_t As) {
-    const int64_t E = int64_t(W) * kWave * Width<DT>::K;
-    const int64_t slots = int64_t(sizeof(float)) * Op::kStaged * (E + 4);
-    const int64_t slabs = 2 * sliced_cap<DT>(W, As) * int64_t(sizeof(DT));
-    return slots > slabs ? slots : slabs;
 }
 
 template <class Op, typename DT>
@@ -269,36 +201,19 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
                                     : kWsRecordsOffset;
     const bool ws_ok = ws && ws_bytes >= ws_need && aligned(ws, 64);
     const int forced = g_variant;
-    if constexpr (Op::kStaged > 0 && Op::kSliced) {
-        // Long action axes: one-wave workgroups, the widest slice that fits the LDS budget.
+    if (forced == 2) {
+        if (!ws_ok) return RLCS_ERR_WORKSPACE;
+        p.split = slots_ok;  // more rows than draw slots: whole rows
+    } else if (forced == 1) {
         p.split = false;
-        p.waves = kStagedWaves;
-        a.A_slice = sliced_width<DT>(kStagedWaves, kSlicedLdsBudget);
-        p.lds_bytes = size_t(sliced_lds_bytes<Op, DT>(kStagedWaves, a.A_slice));
-    } else if constexpr (Op::kStaged > 0) {
-        // Staged policies keep whole rows in one workgroup (chunk loop for long rows).
-        p.split = false;
-        if (staged_lds_bytes<Op, DT>(kSmallWaves, a.A) <= kStagedLdsBudget) p.waves = kSmallWaves;
-        else if (staged_lds_bytes<Op, DT>(kStagedMidWaves, a.A) <= kStagedMidLdsBudget) p.waves = kStagedMidWaves;
-        else if (staged_lds_bytes<Op, DT>(kStagedWaves, a.A) <= kStagedLdsBudget) p.waves = kStagedWaves;
-        else return RLCS_ERR_INVALID_ARG;
-        p.lds_bytes = size_t(staged_lds_bytes<Op, DT>(p.waves, a.A));
     } else {
-        if (forced == 2) {
-            if (!ws_ok) return RLCS_ERR_WORKSPACE;
-            p.split = slots_ok;  // more rows than draw slots: whole rows
-        } else if (forced == 1) {
-            p.split = false;
-        } else {
-            p.split = ws_ok && slots_ok && T % K == 0 && T > E_large && N < kSplitBelowRows;
-        }
-        if (p.split) p.waves = small_tiles ? kSmallWaves : kLargeWaves;
-        else if (T > E_small) p.waves = kLargeWaves;
-        else if (OneWaveRows<Op>::value && T % K == 0 && (int64_t(kWave) * K) % T == 0 && T >= 32 * K)
-            p.waves = 1;  // whole rows per wave, every chunk full
-        else p.waves = kSmallWaves;
-        p.lds_bytes = 0;
+        p.split = ws_ok && slots_ok && T % K == 0 && T > E_large && N < kSplitBelowRows;
     }
+    if (p.split) p.waves = small_tiles ? kSmallWaves : kLargeWaves;
+    else if (T > E_small) p.waves = kLargeWaves;
+    else if (OneWaveRows<Op>::value && T % K == 0 && (int64_t(kWave) * K) % T == 0 && T >= 32 * K)
+        p.waves = 1;  // whole rows per wave, every chunk full
+    else p.waves = kSmallWaves;
     p.wave_rows_log2T = -1;
     p.flat_R = 0;
     p.flat_W = kSmallWaves;
@@ -316,7 +231,7 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
     // 19.6 -> 17.1, 4096x1500 33.0 -> 24.7, 2048x2048 19.7 -> 17.0, 8192x1100 44.1 -> 34.0;
     // 64x4096 even (4.45 -> 4.43).
     const int64_t flat_max = sizeof(DT) == 4 ? E_large : int64_t(kWave) * K;
-    if (Op::kStaged == 0 && !p.split && vec && T > K && T <= flat_max && (N * T) % K == 0 &&
+    if (!p.split && vec && T > K && T <= flat_max && (N * T) % K == 0 &&
         !((T & (T - 1)) == 0 && T <= int64_t(kWave) * K)) {
         int64_t gcd = K, b = T % K;
         while (b) { const int64_t r = gcd % b; gcd = b; b = r; }
@@ -337,7 +252,7 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
             if ((N + R - 1) / R > INT32_MAX) return RLCS_ERR_INVALID_ARG;
         }
     }
-    if (Op::kStaged == 0 && !p.split && vec && T >= K && T <= int64_t(kWave) * K && (T & (T - 1)) == 0) {
+    if (!p.split && vec && T >= K && T <= int64_t(kWave) * K && (T & (T - 1)) == 0) {
         // rows tile a wave exactly: the wave-rows kernel
         if ((N * T + int64_t(kWave) * K - 1) / (int64_t(kWave) * K) > INT32_MAX) return RLCS_ERR_INVALID_ARG;
         int l = 0;
@@ -359,7 +274,7 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
         // When a workgroup's rows do not fill its chunks exactly, every chunk still takes the
         // vector path lane by lane: only the lanes at the ragged ends of the workgroup's range
         // go element-wise.
-        p.pad = vec && Op::kStaged == 0 && T >= K && (T % K != 0 || (p.rows_per_wg * T) % E != 0);
+        p.pad = vec && T >= K && (T % K != 0 || (p.rows_per_wg * T) % E != 0);
     }
 
     if constexpr (Op::kFlags) {
@@ -405,7 +320,6 @@ rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, boo
         p.rows_per_wg = (a.T <= E - slack) ? (E - slack - a.T) / period + 1 : 1;
         if ((a.N + p.rows_per_wg - 1) / p.rows_per_wg > INT32_MAX) return RLCS_ERR_INVALID_ARG;
         p.wave_local = 0;
-        p.lds_bytes = 0;
         p.wave_rows_log2T = -1;
         p.flat_R = 0;
         p.flat_W = kSmallWaves;

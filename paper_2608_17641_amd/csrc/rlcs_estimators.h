@@ -32,8 +32,6 @@ struct Args {
     const void* in[5];     // data inputs, meaning fixed by the policy
     const int32_t* actions;  // full-form Retrace: taken actions [N, T]
     int64_t A;             // full-form Retrace: number of actions
-    int64_t A_slice;       // full-form Retrace, long action axes: actions staged at a time
-    int stage_vec;         // full-form Retrace: Q and pi are 16-byte aligned
     const uint8_t* term;   // [N, T] or null
     const uint8_t* trunc;  // [N, T] or null
     const void* row_value; // [N] bootstrap / carry, or null (= 0)
@@ -50,13 +48,6 @@ struct Args {
     void* ws;              // cross-workgroup carry records (split-row variant only)
 };
 
-// Defaults shared by the policies: no inputs staged through LDS.
-struct OpBase {
-    static constexpr int kStaged = 0;
-    static constexpr bool kSliced = false;  // staged policies: action axis taken in slices
-    static constexpr int staged_index(int) { return -1; }
-};
-
 // Bit helpers over K-bit masks.
 __device__ __forceinline__ bool bit(uint32_t m, int k) { return (m >> k) & 1u; }
 
@@ -70,7 +61,7 @@ __device__ __forceinline__ float successor(bool term, bool trunc, bool edge, flo
 
 // ---------------------------------------------------------------- GAE (Section 3.3.1)
 // in: r, v, bv
-struct GaeOp : OpBase {
+struct GaeOp {
     static constexpr bool kBackward = true;
     static constexpr int kSlots = 3;
     static constexpr int kTruncSlot = 2;  // read only at truncated steps
@@ -115,7 +106,7 @@ struct GaeOp : OpBase {
 
 // ---------------------------------------------------------------- V-Trace (Section 3.3.2)
 // in: r, v, log_rho, bv
-struct VtraceOp : OpBase {
+struct VtraceOp {
     static constexpr bool kBackward = true;
     static constexpr int kSlots = 4;
     static constexpr int kTruncSlot = 3;  // read only at truncated steps
@@ -171,7 +162,7 @@ struct VtraceOp : OpBase {
 
 // ---------------------------------------------------------------- Retrace (Section 3.3.3)
 // in: r, q, eq, log_rho, bv
-struct RetraceOp : OpBase {
+struct RetraceOp {
     static constexpr bool kBackward = true;
     static constexpr int kSlots = 5;
     static constexpr int kTruncSlot = 4;  // read only at truncated steps
@@ -222,96 +213,15 @@ struct RetraceOp : OpBase {
 };
 
 // ---------------------------------------------------------------- full-form Retrace (Section 7.3)
-// Global inputs: in[0] r, in[4] bv (truncated steps only); the [N, T, A] Q-values in[1] and
-// target probabilities in[2], the taken actions and the behaviour probabilities in[3] are
-// reduced per step while the chunk is staged, into three LDS slots:
-//   slot 1: Q(s_t, a_t),  slot 2: E_pi Q(s_t) = sum_a pi(a|s_t) Q(s_t, a),
-//   slot 3: rho_t = pi(a_t|s_t) / mu(a_t|s_t).
-// An action outside [0, A) selects nothing (Q and pi taken as 0). The recurrence is
+// Inputs of the builder: r, Q(s_t, a_t), E_pi Q(s_t), rho_t = pi(a_t|s_t) / mu_t, bv. The middle
+// three are reduced from the [N, T, A] tensors by the kernel of the actions header, the only one
+// that runs this policy (in[0] r, in[1] Q, in[2] pi, in[3] mu, in[4] bv). The recurrence is
 // RetraceOp's with c_t = lambda * min(c_bar, rho_t).
-struct RetraceFullOp : OpBase {
-    static constexpr bool kBackward = true;
+struct RetraceFullOp {
     static constexpr int kSlots = 5;
-    static constexpr int kTruncSlot = 4;  // read only at truncated steps
-    static constexpr bool kFlags = true, kRowValue = true;
-    static constexpr int kNbr = 2;  // E_pi Q and c of the next step, read from the stage
-    static constexpr int kNbrRaw = 1;
-    static constexpr int kStaged = 3;
-    static constexpr int staged_index(int s) { return (s >= 1 && s <= 3) ? s - 1 : -1; }
-    static constexpr bool slot_used(int s, bool trunc) { return s == 0 || (s == 4 && trunc); }
+    static constexpr int kNbr = 2;  // E_pi Q and c of the next step
 
     __device__ static float trace(const Params& P, float rho) { return P.lambda * fminf(P.c_bar, rho); }
-
-    // Staged terms of one step from its rows Q(s_t, .) and pi(.|s_t) (in LDS), its action and
-    // its behaviour probability: v = {Q(s_t, a_t), E_pi Q(s_t), rho_t}. The expectation sums
-    // the actions in order. `rows16`: both rows start on 16-byte boundaries and hold whole
-    // 16-byte blocks, read one block at a time. An action outside [0, A) selects nothing.
-    template <typename DT>
-    __device__ __forceinline__ static void reduce_step(const DT* q_row, const DT* pi_row, int64_t A, bool rows16,
-                                       int32_t act, float mu, float (&v)[kStaged]) {
-        constexpr int kPer = 16 / int(sizeof(DT));
-        float e = 0.f, qa = 0.f, pa = 0.f;
-        if (rows16) {
-            for (int64_t b = 0; b < A / kPer; ++b) {
-                const u32x4 bq = *reinterpret_cast<const u32x4*>(q_row + b * kPer);
-                const u32x4 bp = *reinterpret_cast<const u32x4*>(pi_row + b * kPer);
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const float qk = word_elem<DT>(bq[u * 4 / kPer], u);
-                    const float pk = word_elem<DT>(bp[u * 4 / kPer], u);
-                    e = fmaf(pk, qk, e);
-                    if (b * kPer + u == act) { qa = qk; pa = pk; }
-                }
-            }
-        } else {
-            for (int64_t k = 0; k < A; ++k) {
-                const float qk = widen(q_row[k]), pk = widen(pi_row[k]);
-                e = fmaf(pk, qk, e);
-                if (k == act) { qa = qk; pa = pk; }
-            }
-        }
-        v[0] = qa;
-        v[1] = e;
-        v[2] = pa / mu;
-    }
-    // One slice of a step's rows, actions [a0, a0 + aw) (row pointers at action a0): adds
-    // pi * Q over the slice to `e`, in action order, and takes Q and pi of the taken action if
-    // it lies in the slice. Rows of whole 16-byte blocks are read one block at a time.
-    template <typename DT>
-    __device__ __forceinline__ static void accumulate_slice(const DT* q_row, const DT* pi_row, int64_t a0,
-                                                            int64_t aw, int32_t act, float& e, float& qa,
-                                                            float& pa) {
-        constexpr int kPer = 16 / int(sizeof(DT));
-        if (aw % kPer == 0) {
-            for (int64_t b = 0; b < aw / kPer; ++b) {
-                const u32x4 bq = *reinterpret_cast<const u32x4*>(q_row + b * kPer);
-                const u32x4 bp = *reinterpret_cast<const u32x4*>(pi_row + b * kPer);
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const float qk = word_elem<DT>(bq[u * 4 / kPer], u);
-                    const float pk = word_elem<DT>(bp[u * 4 / kPer], u);
-                    e = fmaf(pk, qk, e);
-                    if (a0 + b * kPer + u == act) { qa = qk; pa = pk; }
-                }
-            }
-        } else {
-            for (int64_t k = 0; k < aw; ++k) {
-                const float qk = widen(q_row[k]), pk = widen(pi_row[k]);
-                e = fmaf(pk, qk, e);
-                if (a0 + k == act) { qa = qk; pa = pk; }
-            }
-        }
-    }
-    __device__ static void nbr_from_stage(const Params& P, const float* stage, int stride, int i,
-                                          float (&nb)[kNbr]) {
-        nb[0] = stage[1 * stride + i];
-        nb[1] = trace(P, stage[2 * stride + i]);
-    }
-    template <int K>
-    __device__ static void nbr_export(const Params&, const float (&)[kSlots][K], uint32_t, float (&)[kNbr]) {}
-    template <typename DT>
-    __device__ static void nbr_load_raw(const Args&, int64_t, float (&)[kNbrRaw]) {}
-    __device__ static void nbr_fix(const Args&, const float (&)[kNbrRaw], float (&)[kNbr]) {}
 
     template <int K, bool TR>
     __device__ static void build(const Params& P, const float (&d)[kSlots][K], uint32_t term,
@@ -336,15 +246,9 @@ struct RetraceFullOp : OpBase {
     }
 };
 
-// Full-form Retrace with the action axis staged in slices (axes too long for a chunk's whole
-// [steps, A] slices in LDS).
-struct RetraceFullSlicedOp : RetraceFullOp {
-    static constexpr bool kSliced = true;
-};
-
 // ---------------------------------------------------------------- TD(lambda) (Section 3.3.4)
 // in: r, v, bv
-struct TdLambdaOp : OpBase {
+struct TdLambdaOp {
     static constexpr bool kBackward = true;
     static constexpr int kSlots = 3;
     static constexpr int kTruncSlot = 2;  // read only at truncated steps
@@ -395,7 +299,7 @@ struct TdLambdaOp : OpBase {
 
 // ---------------------------------------------------------------- discounted returns (Section 3.3.4)
 // in: r, bv
-struct DiscountedOp : OpBase {
+struct DiscountedOp {
     static constexpr bool kBackward = true;
     static constexpr int kSlots = 2;
     static constexpr int kTruncSlot = 1;  // read only at truncated steps
@@ -435,7 +339,7 @@ struct DiscountedOp : OpBase {
 // in: x. kDecay: eligibility traces (gamma lambda) vs. prefix sum (1). kStartsAt: a flag at t
 // cuts the carry into t instead of into t+1.
 template <bool kDecay, bool kStartsAt>
-struct ForwardOp : OpBase {
+struct ForwardOp {
     static constexpr bool kBackward = false;
     static constexpr int kSlots = 1;
     static constexpr int kTruncSlot = -1;
@@ -491,7 +395,7 @@ struct ForwardOp : OpBase {
 // ---------------------------------------------------------------- bare recurrence (Section 4.1)
 // in: alpha, beta; the per-row carry enters at the row edge.
 template <bool kBack>
-struct AffineOp : OpBase {
+struct AffineOp {
     static constexpr bool kBackward = kBack;
     static constexpr int kSlots = 2;
     static constexpr int kTruncSlot = -1;

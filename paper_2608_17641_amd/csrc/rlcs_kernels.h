@@ -115,11 +115,6 @@ __device__ __forceinline__ void advance_idle_slots(void* ws, int64_t used, uint3
 template <bool kBack>
 __device__ __forceinline__ int lane_group(int lane) { return kBack ? (kWave - 1 - lane) : lane; }
 
-// A hook that does nothing.
-struct Nop {
-    __device__ void operator()() const {}
-};
-
 // Row and step of flat positions relative to a base position whose row and step are known:
 // position base.pos + d (0 <= d, base.t + d < 2^31) is in row base.row + q at step r, where
 // (q, r) = divmod(base.t + d, T). The quotient comes from an fp32 reciprocal (inv_T = 1/T) and
@@ -156,12 +151,11 @@ __device__ __forceinline__ void row_and_step(const RowBase& b, int64_t p, int64_
 // the range) takes the element-wise path for its steps in range, which may be none.
 template <class Op, typename DT, int K, int W, bool VEC, bool TR, bool PAD = false>
 struct Chunk {
-    static_assert(!PAD || (VEC && Op::kStaged == 0), "padded rows: vector path, unstaged policies");
+    static_assert(!PAD || VEC, "padded rows: vector path");
     static constexpr bool kBack = Op::kBackward;
     static constexpr int NS = Op::kSlots;
     static constexpr int NB = Op::kNbr > 0 ? Op::kNbr : 1;
     static constexpr uint32_t kAll = (K == 32) ? 0xffffffffu : ((1u << K) - 1u);
-    static constexpr int kStride = W * kWave * K + 4;  // staged slot stride (floats)
 
     float d[NS][K];
     float B[K];
@@ -170,10 +164,9 @@ struct Chunk {
     uint32_t term, trunc, edge, valid;
     int64_t p0;
     int sidx;            // p0 - chunk_lo: the lane's first step within the chunk
-    const float* stage;  // staged slots (policies with kStaged > 0)
-    // Eight outputs per lane, unstaged policies: a wave of a full chunk whose lanes all store
-    // whole vectors holds 512 consecutive outputs, stored as whole lines through its LDS slot.
-    static constexpr bool kLineStores = K == 8 && Op::kStaged == 0;
+    // Eight outputs per lane: a wave of a full chunk whose lanes all store whole vectors holds
+    // 512 consecutive outputs, stored as whole lines through its LDS slot.
+    static constexpr bool kLineStores = K == 8;
     f32x4* oslot = nullptr;
     Pair incl;     // lanes 0..lane of this wave composed (lane 0 innermost)
     Pair wave_in;  // waves between this wave and the chunk's carry-source edge
@@ -188,7 +181,7 @@ struct Chunk {
     // with it (bit for bit). `defer_chunk_`: the chunk defers; `defer_`: this wave does.
     // Four-wave chunks only: with sixteen waves it made one-row-per-workgroup calls slower
     // (eligibility traces 1024 x 4096 fp32 9.9 -> 12.8 us, 256 x 8192 6.6 -> 7.2), unexplained.
-    static constexpr bool kCanDefer = !kBack && Op::kNbr > 0 && Op::kStaged == 0 && !PAD && W == 4;
+    static constexpr bool kCanDefer = !kBack && Op::kNbr > 0 && !PAD && W == 4;
     bool defer_chunk_ = false, defer_ = false;
 
     // Whether lane 0 must read the carry-source neighbour of its edge step from memory: only
@@ -196,15 +189,8 @@ struct Chunk {
     // hence inside the array), and the wave does not take it from LDS later.
     __device__ bool needs_nbr(int lane) const {
         const int ke = kBack ? K - 1 : 0;
-        return Op::kNbr > 0 && Op::kStaged == 0 && lane == 0 && bit(valid, ke) && !bit(edge, ke) &&
+        return Op::kNbr > 0 && lane == 0 && bit(valid, ke) && !bit(edge, ke) &&
                !(kCanDefer && defer_);
-    }
-
-    // Staged slot s (Op::staged_index(s) >= 0) of the lane's K steps, from LDS.
-    __device__ void read_staged(int s, uint32_t mask, bool full) {
-        const float* src = stage + Op::staged_index(s) * kStride + sidx;
-#pragma unroll
-        for (int k = 0; k < K; ++k) d[s][k] = (full || bit(mask, k)) ? src[k] : 0.f;
     }
 
     // Raw words of a FULL chunk's loads, between load_full and convert_full.
@@ -219,13 +205,10 @@ struct Chunk {
     // (their addresses need nothing but p0); the row bookkeeping, the per-row value and the
     // neighbour load follow while they are in flight; a lane reads its truncation
     // continuations only if one of its steps is truncated. No loaded value is used before every
-    // load of the lane has been issued. Staged policies convert later (convert_full after the
-    // stage is complete), so that nothing waits for a load while the staging copies, issued
-    // after the flags, are in flight; they read the continuations unconditionally, since
-    // choosing by the flags would wait for the copies.
-    template <class BaseFn, class PreFn>
+    // load of the lane has been issued.
+    template <class BaseFn>
     __device__ void load_full(const Args& a, int64_t lo, int64_t hi, BaseFn&& base_of, int lane,
-                              float (&nraw)[Op::kNbrRaw], PreFn&& pre) {
+                              float (&nraw)[Op::kNbrRaw]) {
         const int64_t T = a.T;
         int64_t row = 0, t = 0;
         uint32_t in_range = kAll;
@@ -270,7 +253,7 @@ struct Chunk {
                 return;
             }
             if (!vector) {
-                load_masked(a, lo, hi, base_of, lane, nraw, pre);
+                load_masked(a, lo, hi, base_of, lane, nraw);
                 return;
             }
         }
@@ -279,7 +262,6 @@ struct Chunk {
         const uint8_t* fallback = reinterpret_cast<const uint8_t*>(a.in[0]);
         if (Op::kFlags && TR) load_flag_words<K>(a.trunc, p0, rw_);
         if (Op::kFlags) load_flag_words<K>(a.term ? a.term : fallback, p0, tw_);
-        pre();
 #pragma unroll
         for (int s = 0; s < NS; ++s)
             if (Op::slot_used(s, TR) && s != kTS) load_words<DT, K>(a.in[s], p0, w_[s]);
@@ -299,27 +281,21 @@ struct Chunk {
         const bool has_rv = Op::kRowValue && a.row_value;
         rv_raw_ = load_one<DT>(has_rv ? a.row_value : a.in[0], min(row_e, a.N - 1));
         if (needs_nbr(lane)) Op::template nbr_load_raw<DT>(a, kBack ? p0 + K : p0 - 1, nraw);
-        if constexpr (Op::kStaged > 0) {
-            if constexpr (kTS >= 0) load_words<DT, K>(a.in[kTS], p0, w_[kTS]);
-        } else {
-            trunc = (Op::kFlags && TR) ? flag_mask<K>(rw_) : 0u;
-            if constexpr (kTS >= 0) {
-                if (trunc) load_words<DT, K>(a.in[kTS], p0, w_[kTS]);
-                else {
+        trunc = (Op::kFlags && TR) ? flag_mask<K>(rw_) : 0u;
+        if constexpr (kTS >= 0) {
+            if (trunc) load_words<DT, K>(a.in[kTS], p0, w_[kTS]);
+            else {
 #pragma unroll
-                    for (int i = 0; i < kWords; ++i) w_[kTS][i] = 0u;
-                }
+                for (int i = 0; i < kWords; ++i) w_[kTS][i] = 0u;
             }
-            convert_full(a);
         }
+        convert_full(a);
     }
 
     // The conversions of load_full.
     __device__ void convert_full(const Args& a) {
-        if constexpr (Op::kStaged > 0) trunc = (Op::kFlags && TR) ? flag_mask<K>(rw_) : 0u;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if (Op::staged_index(s) >= 0) continue;  // read from LDS in the scan
             if (Op::slot_used(s, TR)) unpack_words<DT, K>(w_[s], d[s]);
             else {
 #pragma unroll
@@ -334,11 +310,10 @@ struct Chunk {
 
     // Step 1 for a chunk with steps outside [lo, hi), or rows with a period above T (their
     // positions t >= T are skipped): element-wise, masked.
-    template <class BaseFn, class PreFn>
+    template <class BaseFn>
     __device__ void load_masked(const Args& a, int64_t lo, int64_t hi, BaseFn&& base_of, int lane,
-                                float (&nraw)[Op::kNbrRaw], PreFn&& pre) {
+                                float (&nraw)[Op::kNbrRaw]) {
         const int64_t T = a.T, Pd = a.period;
-        pre();
         uint32_t inrange = 0;
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -372,7 +347,6 @@ struct Chunk {
         }
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if (Op::staged_index(s) >= 0) continue;  // read from LDS in the scan
             if (Op::slot_used(s, TR)) load_k<DT, K>(a.in[s], p0, s == kTS ? (valid & trunc) : valid, false, d[s]);
             else {
 #pragma unroll
@@ -383,39 +357,24 @@ struct Chunk {
     }
 
     // Steps 1-4. Writes the wave's map to s_a/s_b[wave] unless `wave_local`; the caller
-    // synchronises. Staged policies: `pre` issues the chunk's staging copies (called once the
-    // flag loads are out, so that waiting for the flags does not wait for the copies) and `mid`
-    // completes the stage (called after every load of the lane is issued, before the staged
-    // slots are read).
-    template <bool FULL, class BaseFn, class PreFn, class MidFn>
+    // synchronises.
+    template <bool FULL, class BaseFn>
     __device__ void local_scan(const Args& a, int64_t chunk_lo, int64_t lo, int64_t hi,
                                float* s_a, float* s_b, int lane, int wave, bool wave_local,
-                               BaseFn&& base_of, const float* staged, PreFn&& pre, MidFn&& mid,
-                               float* s_d = nullptr) {
+                               BaseFn&& base_of, float* s_d = nullptr) {
         if constexpr (kCanDefer) {
             defer_chunk_ = FULL && s_d != nullptr && !wave_local;
             defer_ = defer_chunk_ && wave > 0;
         }
         sidx = (wave * kWave + lane_group<kBack>(lane)) * K;
         p0 = chunk_lo + sidx;
-        stage = staged;
         float nraw[Op::kNbrRaw];
-        if (FULL) load_full(a, lo, hi, base_of, lane, nraw, pre);
-        else load_masked(a, lo, hi, base_of, lane, nraw, pre);
-        mid();
-        if constexpr (Op::kStaged > 0) {
-            if (FULL) convert_full(a);
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                if (Op::staged_index(s) >= 0) read_staged(s, valid, FULL);
-        }
+        if (FULL) load_full(a, lo, hi, base_of, lane, nraw);
+        else load_masked(a, lo, hi, base_of, lane, nraw);
 
         // Neighbour on the carry-source side of the lane's edge step: lane l-1 holds it, lane 0
-        // read it from memory; staged policies read it from the stage (which covers one step
-        // past the chunk).
-        if constexpr (Op::kStaged > 0) {
-            Op::nbr_from_stage(a.p, stage, kStride, kBack ? sidx + K : sidx - 1, nb);
-        } else if (Op::kNbr > 0) {
+        // read it from memory.
+        if constexpr (Op::kNbr > 0) {
             float own[NB];
             Op::template nbr_export<K>(a.p, d, term | trunc, own);
 #pragma unroll
@@ -528,14 +487,12 @@ struct Chunk {
 
 // One chunk: local scan, the wave composition (unless rows are wave-local) and, through
 // `carry_of`, the value entering the chunk; then the carry application and stores.
-template <bool FULL, class C, class BaseFn, class CarryFn, class PreFn, class MidFn>
+template <bool FULL, class C, class BaseFn, class CarryFn>
 __device__ __forceinline__ float run_chunk(C& c, const Args& a, int64_t chunk_lo, int64_t lo,
                                            int64_t hi, float* s_a, float* s_b, float* s_d,
                                            int lane, int wave, bool wave_local, BaseFn&& base_of,
-                                           CarryFn&& carry_of, const float* staged, PreFn&& pre,
-                                           MidFn&& mid) {
-    c.template local_scan<FULL>(a, chunk_lo, lo, hi, s_a, s_b, lane, wave, wave_local, base_of,
-                                staged, pre, mid, s_d);
+                                           CarryFn&& carry_of) {
+    c.template local_scan<FULL>(a, chunk_lo, lo, hi, s_a, s_b, lane, wave, wave_local, base_of, s_d);
     if (wave_local) {
         c.wave_in = identity_pair();
     } else {
@@ -545,261 +502,6 @@ __device__ __forceinline__ float run_chunk(C& c, const Args& a, int64_t chunk_lo
     return c.template finish<FULL>(a, carry_of());
 }
 
-// Staging for policies whose per-step terms are reductions over an action axis (full-form
-// Retrace). Steps [chunk_lo, chunk_lo + E] that lie in [lo, N*T) are staged (one step past the
-// chunk, for the neighbour). `issue` starts copying the chunk's [steps, A] slices of Q (in[1])
-// and pi (in[2]) to LDS and loads the steps' actions and behaviour probabilities (in[3]);
-// `commit` completes the copies and, after a barrier, the owner thread of each step (steps
-// tid, tid + blockDim, ...) reduces its slices into the Op::kStaged staged slots. The caller
-// synchronises before the slots are read.
-//
-// Layout of `dyn` (16-byte aligned): the two slices as DT, `cap` elements each, and, over the
-// same bytes once the slices are reduced, kStaged slots of E + 4 floats (the larger of the two is
-// the size staged_lds_bytes on the host assumes). With 16-byte aligned
-// tensors the 16-byte blocks covering a slice go straight from global memory to LDS
-// (global_load_lds_dwordx4: lane l of a wave fills the 16 bytes at the wave-uniform LDS
-// address plus 16*l), with no register round trip and every block of the chunk in flight at
-// once; LDS element 0 is then the first element of the first block. The one block that can
-// reach past the end of the tensors, and the whole slices of unaligned tensors, are copied
-// element-wise.
-template <class Op, typename DT, int E, int J>
-struct Stager {
-    static constexpr int64_t kPerBlock = 16 / int64_t(sizeof(DT));
-    static constexpr int kStride = E + 4;
-    int32_t act[J];
-    float mu[J];
-    int64_t s_lo, s_hi;      // staged steps
-    int64_t el_hi, e0;       // one past the slices' last element; flat element at LDS element 0
-    int64_t el_copy;         // elements [el_copy, el_hi) are copied element-wise
-
-    __device__ static int64_t cap(int64_t A) {
-        return ((int64_t(E + 1) * A + 3 * kPerBlock) / kPerBlock) * kPerBlock;
-    }
-
-    __device__ __forceinline__ void issue(const Args& a, int64_t chunk_lo, int64_t lo, float* dyn) {
-        const int64_t total = a.N * a.T, A = a.A;
-        const int nt = blockDim.x, tid = threadIdx.x;
-        s_lo = max(chunk_lo, lo);
-        s_hi = max(min(chunk_lo + E + 1, total), s_lo);
-        // unconditional loads from a clamped step (s_lo is in range), so that no branch waits
-        // for them
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int64_t i = tid + int64_t(j) * nt;  // stage index
-            const int64_t st = chunk_lo + i;
-            const bool ok = i <= E && st >= s_lo && st < s_hi;
-            const int64_t sc = ok ? st : s_lo;
-            const int32_t act_raw = a.actions[sc];
-            const float mu_raw = load_one<DT>(a.in[3], sc);
-            act[j] = ok ? act_raw : -1;
-            mu[j] = ok ? mu_raw : 1.f;
-        }
-        const int64_t el_lo = s_lo * A;
-        el_hi = s_hi * A;
-        if (!a.stage_vec) {
-            e0 = el_lo;
-            el_copy = el_lo;
-            return;
-        }
-        const int64_t blk_lo = el_lo / kPerBlock;
-        const int64_t nblk = el_hi > el_lo ? (el_hi + kPerBlock - 1) / kPerBlock - blk_lo : 0;
-        const int64_t nfull = min(nblk, max(total * A / kPerBlock - blk_lo, int64_t(0)));
-        e0 = blk_lo * kPerBlock;
-        el_copy = max(el_lo, (blk_lo + nfull) * kPerBlock);
-        const u32x4* gq = reinterpret_cast<const u32x4*>(a.in[1]) + blk_lo;
-        const u32x4* gp = reinterpret_cast<const u32x4*>(a.in[2]) + blk_lo;
-        u32x4* lq = reinterpret_cast<u32x4*>(dyn);
-        u32x4* lp = lq + cap(A) / kPerBlock;
-        const int lane = tid & (kWave - 1);
-        for (int64_t b0 = tid - lane; b0 < nfull; b0 += nt) {
-            if (b0 + lane < nfull) {
-                __builtin_amdgcn_global_load_lds(gq + b0 + lane, (__attribute__((address_space(3))) void*)(lq + b0), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds(gp + b0 + lane, (__attribute__((address_space(3))) void*)(lp + b0), 16, 0, 0);
-            }
-        }
-    }
-
-    __device__ __forceinline__ void commit(const Args& a, int64_t chunk_lo, float* dyn) {
-        const int64_t A = a.A;
-        const int nt = blockDim.x, tid = threadIdx.x;
-        DT* sq = reinterpret_cast<DT*>(dyn);
-        DT* sp = sq + cap(A);
-        const DT* gq = reinterpret_cast<const DT*>(a.in[1]);
-        const DT* gp = reinterpret_cast<const DT*>(a.in[2]);
-        const int64_t n_el = el_hi - el_copy;
-        for (int64_t base = tid; base < n_el; base += 8 * int64_t(nt)) {
-            DT vq[8], vp[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t m = base + int64_t(u) * nt;
-                if (m < n_el) { vq[u] = gq[el_copy + m]; vp[u] = gp[el_copy + m]; }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t m = base + int64_t(u) * nt;
-                if (m < n_el) { sq[el_copy - e0 + m] = vq[u]; sp[el_copy - e0 + m] = vp[u]; }
-            }
-        }
-        // the LDS copies of this wave have landed; then every wave's have
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        // rows are 16-byte aligned whole blocks in LDS when A is a multiple of a block
-        const bool rows16 = a.stage_vec && A % kPerBlock == 0;
-        float v[J][Op::kStaged];
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int64_t i = tid + int64_t(j) * nt;
-            const int64_t st = chunk_lo + i;
-#pragma unroll
-            for (int q = 0; q < Op::kStaged; ++q) v[j][q] = 0.f;
-            if (i <= E && st >= s_lo && st < s_hi) {
-                Op::template reduce_step<DT>(sq + (st * A - e0), sp + (st * A - e0), A, rows16, act[j], mu[j], v[j]);
-                bad = bad || act[j] < 0 || act[j] >= A;
-            }
-        }
-        if (bad && a.ws) report_bad_action(a.ws);
-        // the slots overlay the slices: every slice read is done before any slot is written
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int64_t i = tid + int64_t(j) * nt;
-            if (i > E) continue;
-#pragma unroll
-            for (int q = 0; q < Op::kStaged; ++q) dyn[q * kStride + i] = v[j][q];
-        }
-    }
-};
-
-// Staging for action axes too long for a chunk's whole [steps, A] slices in LDS: the axis is
-// taken in slices of a.A_slice actions (whole 128-byte lines of DT where one fits, else a
-// multiple of 16 bytes). For each slice, the [staged steps, slice] blocks of Q and pi go to
-// LDS (row stride = the slice's width: by
-// global_load_lds_dwordx4 when every row segment is whole aligned 16-byte blocks, element-wise
-// otherwise), and the owner thread of each step adds the slice's terms to its running sums:
-// E_pi Q over the actions in order (the same sequence of fused multiply-adds as one slice
-// holding the whole axis), and Q and pi of the taken action when it lies in the slice. A
-// barrier separates each slice's reads from the next slice's copies, and the last reads from
-// the slots, which overlay the slices as in Stager. The first slice is issued with the chunk's
-// other loads; the others follow one at a time.
-template <class Op, typename DT, int E, int J>
-struct SlicedStager {
-    static constexpr int64_t kPerBlock = 16 / int64_t(sizeof(DT));
-    static constexpr int kStride = E + 4;
-    int32_t act[J];
-    float mu[J];
-    float qa[J], ex[J], pa[J];
-    int64_t s_lo, s_hi;
-
-    // LDS elements of one array's slab of `As` actions (rounded up to whole 16-byte blocks).
-    __device__ static int64_t cap(int64_t As) {
-        return (int64_t(E + 1) * As + kPerBlock - 1) / kPerBlock * kPerBlock;
-    }
-
-    __device__ __forceinline__ void copy_slice(const Args& a, int64_t a0, int64_t aw, float* dyn) {
-        const int64_t A = a.A, rows = s_hi - s_lo;
-        const int nt = blockDim.x, tid = threadIdx.x;
-        DT* sq = reinterpret_cast<DT*>(dyn);
-        DT* sp = sq + cap(a.A_slice);
-        if (a.stage_vec && A % kPerBlock == 0 && aw % kPerBlock == 0) {
-            // a0 is a multiple of the slice width, itself a multiple of kPerBlock
-            const int64_t bpr = aw / kPerBlock, nblk = rows * bpr;
-            const u32x4* gq = reinterpret_cast<const u32x4*>(a.in[1]);
-            const u32x4* gp = reinterpret_cast<const u32x4*>(a.in[2]);
-            u32x4* lq = reinterpret_cast<u32x4*>(sq);
-            u32x4* lp = reinterpret_cast<u32x4*>(sp);
-            const int lane = tid & (kWave - 1);
-            for (int64_t b0 = tid - lane; b0 < nblk; b0 += nt) {
-                const int64_t b = b0 + lane;
-                if (b < nblk) {
-                    const int64_t row = b / bpr, cb = b - row * bpr;
-                    const int64_t g = ((s_lo + row) * A + a0) / kPerBlock + cb;
-                    __builtin_amdgcn_global_load_lds(gq + g, (__attribute__((address_space(3))) void*)(lq + b0), 16, 0, 0);
-                    __builtin_amdgcn_global_load_lds(gp + g, (__attribute__((address_space(3))) void*)(lp + b0), 16, 0, 0);
-                }
-            }
-        } else {
-            const DT* gq = reinterpret_cast<const DT*>(a.in[1]);
-            const DT* gp = reinterpret_cast<const DT*>(a.in[2]);
-            for (int64_t row = tid / aw, c = tid % aw; row < rows;) {
-                const int64_t g = (s_lo + row) * A + a0 + c;
-                sq[row * aw + c] = gq[g];
-                sp[row * aw + c] = gp[g];
-                c += nt;
-                row += c / aw;
-                c %= aw;
-            }
-        }
-    }
-
-    __device__ __forceinline__ void issue(const Args& a, int64_t chunk_lo, int64_t lo, float* dyn) {
-        const int64_t total = a.N * a.T;
-        const int nt = blockDim.x, tid = threadIdx.x;
-        s_lo = max(chunk_lo, lo);
-        s_hi = max(min(chunk_lo + E + 1, total), s_lo);
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int64_t i = tid + int64_t(j) * nt;  // stage index
-            const int64_t st = chunk_lo + i;
-            const bool ok = i <= E && st >= s_lo && st < s_hi;
-            const int64_t sc = ok ? st : s_lo;
-            const int32_t act_raw = a.actions[sc];
-            const float mu_raw = load_one<DT>(a.in[3], sc);
-            act[j] = ok ? act_raw : -1;
-            mu[j] = ok ? mu_raw : 1.f;
-            qa[j] = ex[j] = pa[j] = 0.f;
-        }
-        copy_slice(a, 0, min(a.A_slice, a.A), dyn);
-    }
-
-    __device__ __forceinline__ void commit(const Args& a, int64_t chunk_lo, float* dyn) {
-        const int64_t A = a.A, As = a.A_slice;
-        const int nt = blockDim.x, tid = threadIdx.x;
-        const DT* sq = reinterpret_cast<const DT*>(dyn);
-        const DT* sp = sq + cap(As);
-        for (int64_t a0 = 0;;) {
-            const int64_t aw = min(As, A - a0);
-            // the LDS copies of this wave have landed; then every wave's have
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int64_t i = tid + int64_t(j) * nt;
-                const int64_t st = chunk_lo + i;
-                if (i <= E && st >= s_lo && st < s_hi)
-                    Op::template accumulate_slice<DT>(sq + (st - s_lo) * aw, sp + (st - s_lo) * aw, a0, aw,
-                                                      act[j], ex[j], qa[j], pa[j]);
-            }
-            a0 += aw;
-            if (a0 >= A) break;
-            __syncthreads();  // every read of this slice is done before the next one lands
-            copy_slice(a, a0, min(As, A - a0), dyn);
-        }
-        // the slots overlay the slices: every slice read is done before any slot is written
-        __syncthreads();
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int64_t i = tid + int64_t(j) * nt;
-            if (i > E) continue;
-            const int64_t st = chunk_lo + i;
-            const bool in = st >= s_lo && st < s_hi;
-            bad = bad || (in && (act[j] < 0 || act[j] >= A));
-            float v[Op::kStaged] = {in ? qa[j] : 0.f, in ? ex[j] : 0.f, in ? pa[j] / mu[j] : 0.f};
-#pragma unroll
-            for (int q = 0; q < Op::kStaged; ++q) dyn[q * kStride + i] = v[q];
-        }
-        if (bad && a.ws) report_bad_action(a.ws);
-    }
-};
-
-// Policies without staging.
-template <class Op, typename DT, int E, int J>
-struct NoStager {
-    __device__ void issue(const Args&, int64_t, int64_t, float*) {}
-    __device__ void commit(const Args&, int64_t, float*) {}
-};
-
 // Rows kernel: workgroup g owns rows [g*R, g*R + R) and walks them in chunks of E steps
 // aligned to multiples of K, starting from the carry source (the end for backward scans).
 // `wave_local`: every wave's span starts and ends on row edges (T divides 64*K and the chunk
@@ -808,10 +510,6 @@ template <class Op, typename DT, int K, int W, bool VEC, bool TR, bool PAD = fal
 __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_per_wg, int wave_local) {
     using C = Chunk<Op, DT, K, W, VEC, TR, PAD>;
     constexpr int64_t E = int64_t(W) * kWave * K;
-    using S = std::conditional_t<(Op::kStaged > 0),
-                                 std::conditional_t<Op::kSliced, SlicedStager<Op, DT, int(E), K + 1>,
-                                                    Stager<Op, DT, int(E), K + 1>>,
-                                 NoStager<Op, DT, int(E), K + 1>>;
     __shared__ float s_a[W], s_b[W];
     __shared__ float s_d[C::kCanDefer ? W : 1];
     __shared__ float s_carry;
@@ -824,22 +522,17 @@ __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_pe
     const bool can_full = VEC && a.T >= K && (PAD || a.period == a.T);
     float carry = 0.f;
     auto carry_of = [&]() { return carry; };
-    extern __shared__ __align__(16) float s_dyn[];  // staged policies only (sized at launch)
-    const float* stage = Op::kStaged > 0 ? s_dyn : nullptr;
     // the workgroup's first step is the start of row row_lo
     auto base_of = [&]() { return RowBase{lo, row_lo, 0}; };
     if (Op::kBackward) {
         int64_t chunk_hi = (hi + K - 1) / K * K;
         for (;;) {
             const int64_t chunk_lo = chunk_hi - E;
-            S sg;
-            auto pre = [&]() { sg.issue(a, chunk_lo, lo, s_dyn); };
-            auto mid = [&]() { if constexpr (Op::kStaged > 0) { sg.commit(a, chunk_lo, s_dyn); __syncthreads(); } };
             C c;
             c.oslot = s_out[C::kLineStores ? wave : 0];
             const float first = (can_full && (PAD || (chunk_lo >= lo && chunk_hi <= hi)))
-                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of, stage, pre, mid)
-                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of, stage, pre, mid);
+                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of)
+                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of);
             if (chunk_lo <= lo) break;
             // the next chunk (earlier in time) continues from A at chunk_lo, held by lane 63 of
             // wave 0
@@ -851,14 +544,11 @@ __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_pe
     } else {
         int64_t chunk_lo = lo / K * K;
         for (;;) {
-            S sg;
-            auto pre = [&]() { sg.issue(a, chunk_lo, lo, s_dyn); };
-            auto mid = [&]() { if constexpr (Op::kStaged > 0) { sg.commit(a, chunk_lo, s_dyn); __syncthreads(); } };
             C c;
             c.oslot = s_out[C::kLineStores ? wave : 0];
             const float last = (can_full && (PAD || (chunk_lo >= lo && chunk_lo + E <= hi)))
-                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of, stage, pre, mid)
-                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of, stage, pre, mid);
+                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of)
+                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of);
             if (chunk_lo + E >= hi) break;
             if (threadIdx.x == W * kWave - 1) s_carry = last;
             __syncthreads();
@@ -882,7 +572,6 @@ __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_pe
 // own (no LDS, no barrier). Grid: ceil(N*T / (64*K*WPG)) workgroups of WPG waves.
 template <class Op, typename DT, int K, bool TR, int WPG = 1>
 __global__ void __launch_bounds__(WPG * kWave) wave_rows_kernel(Args a, int log2T) {
-    static_assert(Op::kStaged == 0, "staged policies run on the rows kernel");
     constexpr bool kBack = Op::kBackward;
     constexpr int NS = Op::kSlots;
     constexpr int NB = Op::kNbr > 0 ? Op::kNbr : 1;
@@ -1007,7 +696,6 @@ constexpr int flat_shift(int W) { return W > 4 ? 26 : 22; }
 
 template <class Op, typename DT, int K, bool TR, int W>
 __global__ void __launch_bounds__(W * kWave) flat_rows_kernel(Args a, int R, uint32_t magic) {
-    static_assert(Op::kStaged == 0, "staged policies run on the rows kernel");
     constexpr bool kBack = Op::kBackward;
     constexpr int NS = Op::kSlots;
     constexpr int NB = Op::kNbr > 0 ? Op::kNbr : 1;
@@ -1244,9 +932,8 @@ __global__ void __launch_bounds__(W * kWave) tiles_kernel(Args a, int64_t P) {
     // whole 16-byte vectors: a full tile whose rows start on a vector boundary
     const bool full = VEC && T % K == 0 && hi - lo == E;
     auto base_of = [&]() { return RowBase{lo, row, p * E}; };
-    static_assert(Op::kStaged == 0, "staged policies run on the rows kernel only");
-    if (full) c.template local_scan<true>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of, nullptr, Nop{}, Nop{});
-    else c.template local_scan<false>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of, nullptr, Nop{}, Nop{});
+    if (full) c.template local_scan<true>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of);
+    else c.template local_scan<false>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of);
     __syncthreads();
     c.wave_prefix(s_a, s_b, wave);
 
