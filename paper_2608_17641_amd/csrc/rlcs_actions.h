@@ -48,10 +48,6 @@ __device__ __forceinline__ float group_sum(float v) {
 }
 
 // Raw words of four consecutive elements at any element address.
-typedef u32x4 __attribute__((aligned(4))) u32x4_any;
-typedef u32x2 __attribute__((aligned(2))) u32x2_any;
-typedef f32x4 __attribute__((aligned(4))) f32x4_any;
-typedef uint32_t __attribute__((aligned(1))) flag_word_any;  // flags of four steps
 template <typename DT, bool NT>
 __device__ __forceinline__ void load_any4(const DT* p, uint32_t (&w)[sizeof(DT)]) {
     if constexpr (sizeof(DT) == 4) {
@@ -64,10 +60,6 @@ __device__ __forceinline__ void load_any4(const DT* p, uint32_t (&w)[sizeof(DT)]
         w[0] = u.x; w[1] = u.y;
     }
 }
-
-// Puts an element in place k of raw words (zero before).
-__device__ __forceinline__ void put_element(uint32_t* w, int k, float v) { w[k] = __float_as_uint(v); }
-__device__ __forceinline__ void put_element(uint32_t* w, int k, bf16_t v) { w[k >> 1] |= uint32_t(v.bits) << (16 * (k & 1)); }
 
 // A lane's K steps (1 or 4) of an input from step p0 on, as raw words: one vector load where they
 // all lie in the array (`whole`), else the steps of `mask`.
@@ -91,7 +83,7 @@ __device__ __forceinline__ void load_step_flags(const uint8_t* base, int64_t p0,
     if constexpr (K == 1) {
         if (mask) w = base[p0];
     } else if (whole) {
-        if (mask) w = *reinterpret_cast<const flag_word_any*>(base + p0);
+        if (mask) w = *reinterpret_cast<const flags4_any*>(base + p0);
     } else {
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -383,9 +375,8 @@ __global__ void __launch_bounds__(kActMaxWaves * kWave) action_rows_kernel(Args 
                 if (a.out1) __builtin_nontemporal_store(o1[0], a.out1 + p0);
             }
         } else if (valid == (1u << K) - 1u) {
-            __builtin_nontemporal_store(f32x4{o0[0], o0[1], o0[2], o0[3]}, reinterpret_cast<f32x4_any*>(a.out0 + p0));
-            if (a.out1)
-                __builtin_nontemporal_store(f32x4{o1[0], o1[1], o1[2], o1[3]}, reinterpret_cast<f32x4_any*>(a.out1 + p0));
+            store4_any(a.out0 + p0, f32x4{o0[0], o0[1], o0[2], o0[3]});
+            if (a.out1) store4_any(a.out1 + p0, f32x4{o1[0], o1[1], o1[2], o1[3]});
         } else if (valid) {
             store_k<K>(a.out0, p0, valid, false, o0);
             if (a.out1) store_k<K>(a.out1, p0, valid, false, o1);

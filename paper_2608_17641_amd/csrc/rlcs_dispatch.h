@@ -31,10 +31,6 @@ int64_t resident_groups(Kernel kernel, int threads) {
 // longer rows (one row, or a 16*64*K-step tile of one, per workgroup).
 constexpr int kSmallWaves = 4;
 constexpr int kLargeWaves = 16;
-// Rows of 32*K to 64*K steps (at most two rows per wave, whole rows per wave) run one-wave
-// workgroups for the policies where that measured faster (C harness, cold: 4096 x 256 fp32 GAE
-// 5.76 -> 5.68 us, eligibility traces 3.45 -> 3.38 us, bf16 GAE 16384 x 512 25.6 -> 25.1 us);
-// V-Trace, Retrace and TD(lambda) ran 2-7 % slower so and keep four-wave workgroups.
 // Wave-rows calls of float32 GAE with truncation take workgroups of four waves (each wave still
 // on its own) from 2^18 to 2^20 steps (1024 to 4096 waves), one wave per workgroup otherwise.
 // Measured (C harness, cold, one-wave against four-wave workgroups): 4096 x 256 5.21 -> 4.78 us,
@@ -48,10 +44,6 @@ constexpr int64_t kWaveRowsQuadMinSteps = int64_t(1) << 18;
 constexpr int64_t kWaveRowsQuadSteps = int64_t(1) << 20;
 template <class Op, typename DT, bool TR> struct WaveRowsQuads : std::false_type {};
 template <> struct WaveRowsQuads<GaeOp, float, true> : std::true_type {};
-
-template <class Op> struct OneWaveRows : std::false_type {};
-template <> struct OneWaveRows<GaeOp> : std::true_type {};
-template <bool D, bool S> struct OneWaveRows<ForwardOp<D, S>> : std::true_type {};
 
 // Steps per lane: one 16-byte vector of each input.
 template <typename DT> struct Width;
@@ -110,7 +102,34 @@ struct Plan {
     int flat_R;           // > 0: flat_rows_kernel with this many whole rows per workgroup
     int flat_W;           // its waves per workgroup (4, or 16 for float32 rows)
     uint32_t flat_magic;  // ceil(2^flat_shift(flat_W) / T): a lane's row by multiply-shift
+    int ragged_R;         // > 0: ragged_rows_kernel with this many whole rows per workgroup
+    int ragged_W;         // its waves per workgroup
+    int ragged_grid;      // its lanes' first step is a multiple of this
+    uint32_t ragged_magic;
 };
+
+// The ragged rows kernel's plan for rows of T steps, K <= T <= kRaggedWaves * 64 * K: as many
+// whole rows as fit four waves, or one longer row on as many waves as it needs; the lanes start on
+// the coarsest of a 128-byte line of inputs, a 16-byte vector and a step that leaves them room
+// (a range of R * T steps starts up to `grid` - gcd(R * T, grid) steps past one). More rows to a
+// workgroup gain more than the alignment: GAE 9001 x 201 float32 8.5 us with five rows from any
+// step against 9.3 with four from a line, 9001 x 401 bfloat16 12.6 against 13.9.
+inline void plan_ragged(Plan& p, int64_t T, int64_t K) {
+    const int64_t span = int64_t(kWave) * K, four = kSmallWaves * span;
+    const int64_t R = T < four ? four / T : 1;
+    const int64_t most = R > 1 ? four : kRaggedWaves * span;
+    for (const int64_t grid : {8 * K, K, int64_t(1)}) {
+        int64_t g = grid, b = R * T % grid;
+        while (b) { const int64_t r = g % b; g = b; b = r; }
+        const int64_t steps = R * T + grid - g;
+        if (steps > most) continue;
+        p.ragged_R = int(R);
+        p.ragged_W = int((steps + span - 1) / span);
+        p.ragged_grid = int(grid);
+        p.ragged_magic = R > 1 ? uint32_t(((int64_t(1) << flat_shift(4)) + T - 1) / T) : 0u;
+        return;
+    }
+}
 
 template <class Op, typename DT, bool VEC, bool TR, int W, bool PAD = false>
 void launch_w(const Args& a, const Plan& p, hipStream_t stream) {
@@ -129,6 +148,13 @@ void launch_w(const Args& a, const Plan& p, hipStream_t stream) {
 
 template <class Op, typename DT, bool VEC, bool TR>
 rlcs_status launch(const Args& a, const Plan& p, hipStream_t stream) {
+    if (p.ragged_R > 0) {
+        constexpr int K = Width<DT>::K;
+        hipLaunchKernelGGL((ragged_rows_kernel<Op, DT, K, TR>), dim3(unsigned((a.N + p.ragged_R - 1) / p.ragged_R)),
+                           dim3(unsigned(p.ragged_W * kWave)), K == 8 ? p.ragged_W * 2048 : 0, stream, a,
+                           p.ragged_R, p.ragged_magic, p.ragged_grid);
+        return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
+    }
     if constexpr (VEC) {
         if (p.flat_R > 0) {
             const dim3 grid(unsigned((a.N + p.flat_R - 1) / p.flat_R));
@@ -163,12 +189,6 @@ rlcs_status launch(const Args& a, const Plan& p, hipStream_t stream) {
         if (p.pad && !p.split) {
             if (p.waves == kSmallWaves) launch_w<Op, DT, true, TR, kSmallWaves, true>(a, p, stream);
             else launch_w<Op, DT, true, TR, kLargeWaves, true>(a, p, stream);
-            return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
-        }
-    }
-    if constexpr (OneWaveRows<Op>::value) {
-        if (p.waves == 1) {
-            launch_w<Op, DT, VEC, TR, 1>(a, p, stream);
             return hipGetLastError() == hipSuccess ? RLCS_OK : RLCS_ERR_LAUNCH;
         }
     }
@@ -211,8 +231,6 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
     }
     if (p.split) p.waves = small_tiles ? kSmallWaves : kLargeWaves;
     else if (T > E_small) p.waves = kLargeWaves;
-    else if (OneWaveRows<Op>::value && T % K == 0 && (int64_t(kWave) * K) % T == 0 && T >= 32 * K)
-        p.waves = 1;  // whole rows per wave, every chunk full
     else p.waves = kSmallWaves;
     p.wave_rows_log2T = -1;
     p.flat_R = 0;
@@ -258,6 +276,19 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
         int l = 0;
         while ((int64_t(1) << l) < T) ++l;
         p.wave_rows_log2T = l;
+    }
+    // Other rows of up to sixteen waves run on the ragged rows kernel, except rows that fill a
+    // four-wave chunk of the rows kernel exactly (aligned arrays; bfloat16 rows of 1024 and 2048
+    // steps: eligibility traces 16384 x 1024 23.3 us there against 26.0, GAE 16384 x 2048 85.5
+    // against 86.9). Measured against the rows kernel, which they took before, lane by lane or
+    // one sixteen-wave workgroup per row: V-Trace 4096 x 2001 float32 43.6 -> 33.8 us, GAE 4096 x
+    // 4095 106 -> 60, TD(lambda) 5001 x 3001 78.8 -> 43.4, GAE 9001 x 15 4.5 -> 3.5; bfloat16
+    // V-Trace 8192 x 3001 113 -> 73, 8192 x 4096 122 -> 98, 8192 x 1500 44.2 -> 38.2, GAE 4096 x
+    // 8192 98 -> 90, 16384 x 1000 46.1 -> 44.9, 300 x 4000 8.2 -> 8.0.
+    if (!p.split && p.flat_R == 0 && p.wave_rows_log2T < 0 && T >= K && T <= E_large &&
+        (!vec || T % K || E_small % T)) {
+        plan_ragged(p, T, K);
+        if (p.ragged_R > 0 && (N + p.ragged_R - 1) / p.ragged_R > INT32_MAX) return RLCS_ERR_INVALID_ARG;
     }
     if (p.split) {
         if (N * p.tiles_per_row > INT32_MAX) return RLCS_ERR_INVALID_ARG;

@@ -693,6 +693,7 @@ __global__ void __launch_bounds__(WPG * kWave) wave_rows_kernel(Args a, int log2
 // takes sixteen waves only for rows of more than 256 steps). No chunk loop, no element-wise
 // path. Grid: ceil(N / R) workgroups.
 constexpr int flat_shift(int W) { return W > 4 ? 26 : 22; }
+constexpr int kRaggedWaves = 16;  // most waves of a ragged_rows_kernel workgroup
 
 template <class Op, typename DT, int K, bool TR, int W>
 __global__ void __launch_bounds__(W * kWave) flat_rows_kernel(Args a, int R, uint32_t magic) {
@@ -836,6 +837,171 @@ __global__ void __launch_bounds__(W * kWave) flat_rows_kernel(Args a, int R, uin
     } else if (live) {
         store_k<K>(a.out0, p0, 0u, true, o0);
         if (a.out1) store_k<K>(a.out1, p0, 0u, true, o1);
+    }
+}
+
+// Rows of any length T >= K and arrays of any element alignment, dense: what flat_rows_kernel does
+// for ranges that neither start nor end on a vector. Workgroup g of W = blockDim / 64 waves (16 at
+// most) owns rows [g*R, g*R + R), the range [lo, hi); its lanes take consecutive groups of K steps
+// from `base`, lo rounded down to a multiple of `grid` steps (a 128-byte line of inputs where the
+// range leaves room for that, so that a wave's vectors and stores fill whole lines; every other
+// alignment costs the same, one line more per wave and array). The lanes that straddle lo or hi
+// load whole vectors too, inside the array, and drop the steps outside the range: the identity
+// for the scan, element stores. Only a lane past the array's last whole vector loads its
+// steps one by one. A lane's first step in the range is o steps from lo; its row is
+// floor(o * magic / 2^22) (flat_rows_kernel), taken for R > 1 only, with o < 1024 (float32) or
+// 2048 (bfloat16); with R = 1, magic is 0. T >= K: at most one row edge among a lane's steps.
+template <class Op, typename DT, int K, bool TR>
+__global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args a, int R, uint32_t magic, int grid) {
+    constexpr bool kBack = Op::kBackward;
+    constexpr int NS = Op::kSlots;
+    constexpr int NB = Op::kNbr > 0 ? Op::kNbr : 1;
+    constexpr int kWords = K * int(sizeof(DT)) / 4;
+    constexpr int kTS = TR ? Op::kTruncSlot : -1;
+    constexpr uint32_t kAll = (1u << K) - 1u;
+    __shared__ float s_a[kRaggedWaves], s_b[kRaggedWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, W = blockDim.x / kWave;
+    const int64_t T = a.T, total = a.N * T;
+    const int64_t row0 = int64_t(blockIdx.x) * R;
+    const int64_t lo = row0 * T;
+    const int64_t hi = min(row0 + R, a.N) * T;
+    const int64_t base = lo & -int64_t(grid);
+    const int g = lane_group<kBack>(lane);
+    const int64_t p0 = base + (wave * kWave + g) * K;
+    const int k_lo = p0 < lo ? int(min(lo - p0, int64_t(K))) : 0;       // the lane's steps in the
+    const int k_hi = p0 < hi ? int(min(hi - p0, int64_t(K))) : 0;       // range: [k_lo, k_hi)
+    const uint32_t valid = k_lo < k_hi ? (kAll >> (K - k_hi)) & (kAll << k_lo) : 0u;
+    const bool live = valid != 0, whole = live && p0 + K <= total;
+
+    uint32_t tw[(K + 3) / 4] = {}, rw[(K + 3) / 4] = {};
+    uint32_t w[NS][kWords] = {};
+    float nraw[Op::kNbrRaw] = {};
+    if (whole) {
+        const uint8_t* fallback = reinterpret_cast<const uint8_t*>(a.in[0]);
+        if (Op::kFlags && TR) load_flag_words_any<K>(a.trunc, p0, rw);
+        if (Op::kFlags) load_flag_words_any<K>(a.term ? a.term : fallback, p0, tw);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (Op::slot_used(s, TR) && s != kTS) load_words_any<DT, K>(a.in[s], p0, w[s]);
+    } else if (live) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!bit(valid, k)) continue;
+            if (Op::kFlags && TR) rw[k >> 2] |= uint32_t(a.trunc[p0 + k]) << (8 * (k & 3));
+            if (Op::kFlags && a.term) tw[k >> 2] |= uint32_t(a.term[p0 + k]) << (8 * (k & 3));
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (Op::slot_used(s, TR) && s != kTS) put_element(w[s], k, static_cast<const DT*>(a.in[s])[p0 + k]);
+        }
+    }
+    // lane 0: the step past its carry-source edge, from memory (used unless a row edge comes
+    // first; an address outside the range is replaced by one of the lane's own steps)
+    if constexpr (Op::kNbr > 0) {
+        const int64_t pn = kBack ? p0 + K : p0 - 1;
+        if (lane == 0 && live) Op::template nbr_load_raw<DT>(a, pn >= lo && pn < hi ? pn : p0 + k_lo, nraw);
+    }
+    // the row edge among the lane's steps, if any: backward the last step of its first row,
+    // forward the first step of a row
+    const int o = int(p0 - lo) + k_lo;  // the lane's first step in the range, from lo
+    const int r_in = int((uint32_t(o) * magic) >> flat_shift(4));
+    const int t = o - r_in * int(T);
+    int ke = -1;
+    if (kBack) ke = k_lo + int(T) - 1 - t;
+    else ke = t == 0 ? k_lo : k_lo + int(T) - t;
+    const uint32_t edge = (live && ke < K) ? (1u << ke) & valid : 0u;
+    const int64_t row_e = row0 + r_in + ((!kBack && ke > k_lo) ? 1 : 0);
+    const bool has_rv = Op::kRowValue && a.row_value;
+    const float rv = (has_rv && edge) ? load_one<DT>(a.row_value, row_e) : 0.f;
+    const uint32_t trunc = (Op::kFlags && TR) ? flag_mask<K>(rw) & valid : 0u;
+    if constexpr (kTS >= 0) {
+        if (trunc) {
+            if (whole) {
+                load_words_any<DT, K>(a.in[kTS], p0, w[kTS]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (bit(trunc, k)) put_element(w[kTS], k, static_cast<const DT*>(a.in[kTS])[p0 + k]);
+            }
+        }
+    }
+    float d[NS][K];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        if (Op::slot_used(s, TR)) unpack_words<DT, K>(w[s], d[s]);
+        else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) d[s][k] = 0.f;
+        }
+    }
+    const uint32_t term = (Op::kFlags && a.term) ? flag_mask<K>(tw) & valid : 0u;
+    float B[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) B[k] = bit(edge, k) ? rv : 0.f;
+
+    // neighbour on the carry-source side: lane l-1, or for lane 0 the step read from memory
+    float nb[NB];
+    if constexpr (Op::kNbr > 0) {
+        float own[NB];
+        Op::template nbr_export<K>(a.p, d, term | trunc, own);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) nb[i] = shift_up1(own[i], 0.f);
+        if (lane == 0 && live && !(edge & (kBack ? (1u << (K - 1)) : 1u))) Op::nbr_fix(a, nraw, nb);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) nb[i] = 0.f;
+    }
+    float al[K], be[K];
+    Op::template build<K, TR>(a.p, d, term, trunc, edge, B, nb, al, be);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (!bit(valid, k)) { al[k] = 0.f; be[k] = 1.f; }
+    Pair agg;
+    if (kBack) {
+        agg = Pair{al[K - 1], be[K - 1]};
+#pragma unroll
+        for (int k = K - 2; k >= 0; --k) agg = compose(Pair{al[k], be[k]}, agg);
+    } else {
+        agg = Pair{al[0], be[0]};
+#pragma unroll
+        for (int k = 1; k < K; ++k) agg = compose(Pair{al[k], be[k]}, agg);
+    }
+    const Pair incl = wave_scan_inclusive(agg, lane);
+    // the waves on this wave's carry-source side, composed (the range's carry-source end is a
+    // row edge, so nothing enters the range)
+    if (lane == kWave - 1) { s_a[wave] = incl.a; s_b[wave] = incl.b; }
+    __syncthreads();
+    Pair win = identity_pair();
+    if (kBack) {
+        for (int j = W - 1; j > wave; --j) win = compose(Pair{s_a[j], s_b[j]}, win);
+    } else {
+        for (int j = 0; j < wave; ++j) win = compose(Pair{s_a[j], s_b[j]}, win);
+    }
+    const float Xw = win.a;
+    const float X = shift_up1(apply(incl, Xw), Xw);
+    float A[K];
+    if (kBack) {
+        float nxt = X;
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) { A[k] = fmaf(be[k], nxt, al[k]); nxt = A[k]; }
+    } else {
+        float prv = X;
+#pragma unroll
+        for (int k = 0; k < K; ++k) { A[k] = fmaf(be[k], prv, al[k]); prv = A[k]; }
+    }
+    float o0[K], o1[K];
+    Op::template finish<K, TR>(a.p, d, term, trunc, edge, B, nb, A, X, o0, o1);
+    if constexpr (K == 8) {
+        extern __shared__ f32x4 s_out[];  // 2 KB per wave
+        const int64_t wbase = base + int64_t(wave) * kWave * K;
+        f32x4* slot = s_out + wave * 2 * kWave;
+        store8_lines_any(a.out0, wbase, lo, hi, g, lane, o0, slot);
+        if (a.out1) store8_lines_any(a.out1, wbase, lo, hi, g, lane, o1, slot);
+    } else if (valid == kAll) {
+        store4_any(a.out0 + p0, f32x4{o0[0], o0[1], o0[2], o0[3]});
+        if (a.out1) store4_any(a.out1 + p0, f32x4{o1[0], o1[1], o1[2], o1[3]});
+    } else if (live) {
+        store_k<K>(a.out0, p0, valid, false, o0);
+        if (a.out1) store_k<K>(a.out1, p0, valid, false, o1);
     }
 }
 
