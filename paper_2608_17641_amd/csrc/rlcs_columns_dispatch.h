@@ -5,6 +5,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "rlcs_colvec.h"
 #include "rlcs_columns.h"
 #include "rlcs_dispatch.h"
 
@@ -203,6 +204,41 @@ void col_launch(const Args& a, const ColGeom& g, bool split, int64_t blocks, hip
     col_launch_nt<Op, DT, TR, true>(a, g, split, blocks, s);
 }
 
+// Columns from which the automatic choice walks them four to a lane: enough 4 * LC-column blocks to
+// fill the chip without splitting time. Below (time-major GAE float32 T x N = 256 x 4096 6.1 us on
+// narrow groups against 6.9, TD(lambda) 1000 x 4000 19.0 split against 23.1) the other column
+// kernels win.
+constexpr int64_t kColVecMin = 8192;
+
+// Lanes side by side of cols_vec_kernel, or 0 where it does not apply (columns not adjacent, or a
+// batch row's not a multiple of four).
+//   Rows that start on 128-byte lines: blocks of one line of float32 (LC = 8) or bfloat16 (16), the
+//   latter halved where whole lines leave CUs idle; time-major GAE float32 T x N = 256 x 8192 8.7 us
+//   (9.3 on the other kernels), 1000 x 8192 29.5 (40), 256 x 16384 15.8 (17.9), V-Trace 512 x
+//   8192 18.3 (22.7), 100 x 40000 20.0 (23.4); bfloat16 GAE 256 x 8192 8.1 (9.4), 1024 x 16384 54 (85).
+//   Other rows: two blocks to a line, LC = 16, so that fewer lines are shared (GAE float32 768 x 9762
+//   37.6 us, 51.5 with LC = 8, 44.3 before; V-Trace bfloat16 100 x 10000 7.9, 8.7, 8.9).
+//   Many long columns: LC = 32, fewer and longer pieces of each row at a time (GAE float32 1024 x
+//   32768 122 us against 129 and 152 with LC = 16 and 8, 249 x 65536 64.7 against 69.5 and 73.8;
+//   bfloat16 V-Trace 500 x 30000 58 against 63 and 76, 94 before).
+//   Columns of at most 32 steps, one chunk of the other kernels, stay there in float32 (GAE 20 x
+//   8192 3.8 us against 4.2); bfloat16 gains (TD(lambda) 17 x 50000 7.0 -> 5.6).
+//   Vector traces: N x T x F = 64 x 1024 x 256 23.2 us with LC = 8 (29.7 before), 27.3 with 16;
+//   1000 x 200 x 100 42.3 with 16 (44.6), bfloat16 500 x 256 x 256 32.6 with 16 (47); of features
+//   that do not fill lines only in many columns (100 x 1000 x 100 25.6 us split, 32.3 here).
+inline int colvec_lanes(const ColGeom& g, int64_t T, rlcs_dtype dtype) {
+    if (g.J < kColVecMin || g.J > int64_t(INT32_MAX)) return 0;
+    if (g.fcol ? (g.C != 1 || g.bstride != 1) : g.C % kCvV != 0) return 0;
+    const bool f32 = dtype == RLCS_F32;
+    const bool lines = g.st * int64_t(dtype_size(dtype)) % 128 == 0;
+    if (!g.fcol) return g.J >= 32768 ? 16 : lines ? 8 : 0;
+    if (f32 && T <= 32) return 0;
+    if (g.J >= 24576 && T > 192) return 32;
+    if (!lines) return 16;
+    if (g.J >= 49152) return f32 ? 16 : 8;
+    return f32 || g.J < 16384 ? 8 : 16;
+}
+
 template <class Op>
 rlcs_status col_dispatch(Args& a, const ColGeom& g, rlcs_dtype dtype, bool has_trunc, void* ws,
                          size_t ws_bytes, rlcs_stream_t stream) {
@@ -213,6 +249,12 @@ rlcs_status col_dispatch(Args& a, const ColGeom& g, rlcs_dtype dtype, bool has_t
     const bool ws_ok = ws && need > 0 && ws_bytes >= need && aligned(ws, 64) &&
                        blocks <= int64_t(UINT32_MAX) / P;
     const int forced = g_variant;
+    if (forced == 0) {
+        if (const int lc = colvec_lanes(g, a.T, dtype)) {
+            return colvec_launch<Op>(a, g, dtype, Op::kFlags && has_trunc, lc, reinterpret_cast<hipStream_t>(stream))
+                       ? RLCS_OK : RLCS_ERR_LAUNCH;
+        }
+    }
     const int64_t ngroups = dtype == RLCS_BF16 ? narrow_groups<bf16_t>(g.J) : narrow_groups<float>(g.J);
     if (forced == 3 || (forced == 0 && a.T <= kNarrowChunk && ngroups >= kNarrowMinGroups &&
                         ngroups <= kNarrowMaxGroups)) {

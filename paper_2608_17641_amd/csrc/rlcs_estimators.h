@@ -74,6 +74,7 @@ struct GaeOp {
         nb[0] = d[1][0];
     }
     static constexpr int kNbrRaw = kNbr;
+    static constexpr int nbr_slot(int) { return 1; }  // input that value n is read from
     template <typename DT>
     __device__ static void nbr_load_raw(const Args& a, int64_t p, float (&raw)[kNbrRaw]) {
         raw[0] = load_one<DT>(a.in[1], p);
@@ -119,6 +120,7 @@ struct VtraceOp {
         nb[0] = d[1][0];
     }
     static constexpr int kNbrRaw = kNbr;
+    static constexpr int nbr_slot(int) { return 1; }  // input that value n is read from
     template <typename DT>
     __device__ static void nbr_load_raw(const Args& a, int64_t p, float (&raw)[kNbrRaw]) {
         raw[0] = load_one<DT>(a.in[1], p);
@@ -179,6 +181,7 @@ struct RetraceOp {
         nb[1] = trace(P, d[3][0]);
     }
     static constexpr int kNbrRaw = kNbr;
+    static constexpr int nbr_slot(int n) { return 2 + n; }  // input that value n is read from
     template <typename DT>
     __device__ static void nbr_load_raw(const Args& a, int64_t p, float (&raw)[kNbrRaw]) {
         raw[0] = load_one<DT>(a.in[2], p);
@@ -261,6 +264,7 @@ struct TdLambdaOp {
         nb[0] = d[1][0];
     }
     static constexpr int kNbrRaw = kNbr;
+    static constexpr int nbr_slot(int) { return 1; }  // input that value n is read from
     template <typename DT>
     __device__ static void nbr_load_raw(const Args& a, int64_t p, float (&raw)[kNbrRaw]) {
         raw[0] = load_one<DT>(a.in[1], p);
