@@ -3,7 +3,9 @@
 Thin PyTorch binding over the C ABI of ``include/rlcs.h``: every function below checks its
 tensors, passes their device pointers, sizes and the current HIP stream to the function of the
 same name in ``librlcs.so``, and returns the output tensors. All arithmetic runs in the HIP
-kernels; there is no other code path.
+kernels; there is no other code path. Each function first offers the call to its native twin
+(``csrc/binding.cpp``: the same checks, allocations and call, without the interpreter), which takes
+it if every argument is plain and answers NotImplemented otherwise.
 
 Tensors: data inputs are ``[N, T]`` contiguous float32 or bfloat16 (all of one call share the
 dtype), flags are ``[N, T]`` uint8 or bool, ``boot`` / ``carry`` are ``[N]`` of the data dtype,
@@ -30,6 +32,15 @@ __all__ = [
     "rlcs_workspace_size_columns", "make_workspace_columns", "rlcs_gae_masked",
     "rlcs_workspace_size_masked", "rlcs_gae_masked_noalloc",
 ]
+
+_fast = None  # the native functions, once loaded
+
+
+def _load_fast():
+    global _fast
+    _fast = _native.binding()
+    return _fast
+
 
 _DTYPES = {torch.float32: _native.RLCS_F32, torch.bfloat16: _native.RLCS_BF16}
 
@@ -145,6 +156,10 @@ def testing_set_variant(variant: int) -> None:
 
 def rlcs_gae(r, v, term=None, trunc=None, bv=None, boot=None, adv=None, ret=None, *,
              gamma: float, lam: float, ws=None, want_ret: bool = True) -> Tuple[torch.Tensor, Optional[torch.Tensor]]:
+    done = (_fast or _load_fast()).gae(r, v, term, trunc, bv, boot, adv, ret, gamma, lam, ws,
+        want_ret)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("bv", bv, N, T, dt, dev)
     _check_data("boot", boot, N, T, dt, dev, shape=(N,))
@@ -161,6 +176,10 @@ def rlcs_gae(r, v, term=None, trunc=None, bv=None, boot=None, adv=None, ret=None
 def rlcs_vtrace(r, v, log_rho, term=None, trunc=None, bv=None, boot=None, vs=None, pg=None, *,
                 gamma: float, rho_bar: float = 1.0, c_bar: float = 1.0, ws=None,
                 want_pg: bool = True):
+    done = (_fast or _load_fast()).vtrace(r, v, log_rho, term, trunc, bv, boot, vs, pg, gamma,
+        rho_bar, c_bar, ws, want_pg)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("log_rho", log_rho, N, T, dt, dev)
     _check_data("bv", bv, N, T, dt, dev); _check_data("boot", boot, N, T, dt, dev, shape=(N,))
@@ -178,6 +197,10 @@ def rlcs_vtrace(r, v, log_rho, term=None, trunc=None, bv=None, boot=None, vs=Non
 def rlcs_retrace(r, q, eq, log_rho, term=None, trunc=None, bv=None, boot=None, delta=None,
                  q_ret=None, *, gamma: float, lam: float, c_bar: float = 1.0, ws=None,
                  want_q_ret: bool = True):
+    done = (_fast or _load_fast()).retrace(r, q, eq, log_rho, term, trunc, bv, boot, delta, q_ret,
+        gamma, lam, c_bar, ws, want_q_ret)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     for name, t in (("q", q), ("eq", eq), ("log_rho", log_rho), ("bv", bv)):
         _check_data(name, t, N, T, dt, dev)
@@ -199,6 +222,10 @@ def rlcs_retrace_full(r, q, pi, actions, mu, term=None, trunc=None, bv=None, boo
     """Full-form Retrace: q, pi [N, T, A] (data dtype), actions int32 [N, T], mu [N, T]. With a
     zero-filled `ws` of at least 64 bytes, a call that meets an action outside [0, A) sets the
     int32 at byte 8 of `ws` to 2 (the step takes Q and pi as 0)."""
+    done = (_fast or _load_fast()).retrace_full(r, q, pi, actions, mu, term, trunc, bv, boot, delta,
+        q_ret, gamma, lam, c_bar, ws, want_q_ret)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     if not isinstance(q, torch.Tensor) or q.dim() != 3 or tuple(q.shape[:2]) != (N, T):
         raise ValueError("q must be a [N, T, A] tensor")
@@ -222,6 +249,9 @@ def rlcs_retrace_full(r, q, pi, actions, mu, term=None, trunc=None, bv=None, boo
 
 def rlcs_td_lambda(r, v, term=None, trunc=None, bv=None, boot=None, ret=None, *, gamma: float,
                    lam: float, ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).td_lambda(r, v, term, trunc, bv, boot, ret, gamma, lam, ws)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("bv", bv, N, T, dt, dev)
     _check_data("boot", boot, N, T, dt, dev, shape=(N,))
@@ -236,6 +266,9 @@ def rlcs_td_lambda(r, v, term=None, trunc=None, bv=None, boot=None, ret=None, *,
 
 def rlcs_discounted(r, term=None, trunc=None, bv=None, boot=None, ret=None, *, gamma: float,
                     ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).discounted(r, term, trunc, bv, boot, ret, gamma, ws)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("bv", bv, N, T, dt, dev); _check_data("boot", boot, N, T, dt, dev, shape=(N,))
     _check_flags("term", term, N, T, dev); _check_flags("trunc", trunc, N, T, dev)
@@ -249,6 +282,9 @@ def rlcs_discounted(r, term=None, trunc=None, bv=None, boot=None, ret=None, *, g
 
 def rlcs_elig_trace(x, term=None, trunc=None, z=None, *, gamma: float, lam: float,
                     ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).elig_trace(x, term, trunc, z, gamma, lam, ws)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(x)
     _check_flags("term", term, N, T, dev); _check_flags("trunc", trunc, N, T, dev)
     z = _out("z", z, N, T, dev)
@@ -261,6 +297,10 @@ def rlcs_elig_trace(x, term=None, trunc=None, z=None, *, gamma: float, lam: floa
 
 def rlcs_episodic_prefix(x, term=None, trunc=None, c=None, *, boundary: str = "ends_at",
                          ws=None) -> torch.Tensor:
+    if boundary in ("ends_at", "starts_at"):
+        done = (_fast or _load_fast()).episodic_prefix(x, term, trunc, c, boundary == "starts_at", ws)
+        if done is not NotImplemented:
+            return done
     N, T, dt, dev = _prep(x)
     if boundary not in ("ends_at", "starts_at"):
         raise ValueError(f"boundary must be 'ends_at' or 'starts_at', got {boundary!r}")
@@ -276,6 +316,9 @@ def rlcs_episodic_prefix(x, term=None, trunc=None, c=None, *, boundary: str = "e
 
 def rlcs_affine_scan(alpha, beta, carry=None, out=None, *, reverse: bool = True,
                      ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).affine_scan(alpha, beta, carry, out, reverse, ws)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(alpha)
     _check_data("beta", beta, N, T, dt, dev); _check_data("carry", carry, N, T, dt, dev, shape=(N,))
     out = _out("out", out, N, T, dev)
@@ -362,6 +405,10 @@ def rlcs_workspace_size_columns(columns: int, T: int) -> int:
 
 def rlcs_gae_strided(r, v, term=None, trunc=None, bv=None, boot=None, adv=None, ret=None, *,
                      gamma: float, lam: float, ws=None, want_ret: bool = True):
+    done = (_fast or _load_fast()).gae_strided(r, v, term, trunc, bv, boot, adv, ret, gamma, lam,
+        ws, want_ret)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(r)
     _check_strided("v", v, N, T, sn, st, dev, dt); _check_strided("bv", bv, N, T, sn, st, dev, dt)
     _check_strided("term", term, N, T, sn, st, dev, flags=True)
@@ -379,6 +426,10 @@ def rlcs_gae_strided(r, v, term=None, trunc=None, bv=None, boot=None, adv=None, 
 def rlcs_vtrace_strided(r, v, log_rho, term=None, trunc=None, bv=None, boot=None, vs=None,
                         pg=None, *, gamma: float, rho_bar: float = 1.0, c_bar: float = 1.0,
                         ws=None, want_pg: bool = True):
+    done = (_fast or _load_fast()).vtrace_strided(r, v, log_rho, term, trunc, bv, boot, vs, pg,
+        gamma, rho_bar, c_bar, ws, want_pg)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(r)
     for name, t in (("v", v), ("log_rho", log_rho), ("bv", bv)):
         _check_strided(name, t, N, T, sn, st, dev, dt)
@@ -398,6 +449,10 @@ def rlcs_vtrace_strided(r, v, log_rho, term=None, trunc=None, bv=None, boot=None
 def rlcs_retrace_strided(r, q, eq, log_rho, term=None, trunc=None, bv=None, boot=None,
                          delta=None, q_ret=None, *, gamma: float, lam: float, c_bar: float = 1.0,
                          ws=None, want_q_ret: bool = True):
+    done = (_fast or _load_fast()).retrace_strided(r, q, eq, log_rho, term, trunc, bv, boot, delta,
+        q_ret, gamma, lam, c_bar, ws, want_q_ret)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(r)
     for name, t in (("q", q), ("eq", eq), ("log_rho", log_rho), ("bv", bv)):
         _check_strided(name, t, N, T, sn, st, dev, dt)
@@ -416,6 +471,10 @@ def rlcs_retrace_strided(r, q, eq, log_rho, term=None, trunc=None, bv=None, boot
 
 def rlcs_td_lambda_strided(r, v, term=None, trunc=None, bv=None, boot=None, ret=None, *,
                            gamma: float, lam: float, ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).td_lambda_strided(r, v, term, trunc, bv, boot, ret, gamma, lam,
+        ws)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(r)
     _check_strided("v", v, N, T, sn, st, dev, dt); _check_strided("bv", bv, N, T, sn, st, dev, dt)
     _check_strided("term", term, N, T, sn, st, dev, flags=True)
@@ -431,6 +490,9 @@ def rlcs_td_lambda_strided(r, v, term=None, trunc=None, bv=None, boot=None, ret=
 
 def rlcs_discounted_strided(r, term=None, trunc=None, bv=None, boot=None, ret=None, *,
                             gamma: float, ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).discounted_strided(r, term, trunc, bv, boot, ret, gamma, ws)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(r)
     _check_strided("bv", bv, N, T, sn, st, dev, dt)
     _check_strided("term", term, N, T, sn, st, dev, flags=True)
@@ -446,6 +508,9 @@ def rlcs_discounted_strided(r, term=None, trunc=None, bv=None, boot=None, ret=No
 
 def rlcs_elig_trace_strided(x, term=None, trunc=None, z=None, *, gamma: float, lam: float,
                             ws=None) -> torch.Tensor:
+    done = (_fast or _load_fast()).elig_trace_strided(x, term, trunc, z, gamma, lam, ws)
+    if done is not NotImplemented:
+        return done
     N, T, sn, st, dt, dev = _prep_strided(x)
     _check_strided("term", term, N, T, sn, st, dev, flags=True)
     _check_strided("trunc", trunc, N, T, sn, st, dev, flags=True)
@@ -459,6 +524,10 @@ def rlcs_elig_trace_strided(x, term=None, trunc=None, z=None, *, gamma: float, l
 
 def rlcs_episodic_prefix_strided(x, term=None, trunc=None, c=None, *, boundary: str = "ends_at",
                                  ws=None) -> torch.Tensor:
+    if boundary in ("ends_at", "starts_at"):
+        done = (_fast or _load_fast()).episodic_prefix_strided(x, term, trunc, c, boundary == "starts_at", ws)
+        if done is not NotImplemented:
+            return done
     N, T, sn, st, dt, dev = _prep_strided(x)
     if boundary not in ("ends_at", "starts_at"):
         raise ValueError(f"boundary must be 'ends_at' or 'starts_at', got {boundary!r}")
@@ -478,6 +547,9 @@ def rlcs_episodic_prefix_strided(x, term=None, trunc=None, c=None, *, boundary: 
 def rlcs_elig_trace_vec(x, term=None, trunc=None, z=None, *, gamma: float, lam: float,
                         ws=None) -> torch.Tensor:
     """x: contiguous [N, T, F] float32 / bfloat16; flags [N, T]; returns float32 z [N, T, F]."""
+    done = (_fast or _load_fast()).elig_trace_vec(x, term, trunc, z, gamma, lam, ws)
+    if done is not NotImplemented:
+        return done
     if not isinstance(x, torch.Tensor) or x.dim() != 3:
         raise ValueError("x must be a 3-D [N, T, F] tensor")
     if x.dtype not in _DTYPES:
@@ -512,6 +584,10 @@ def rlcs_gae_masked(r, v, mask=None, term=None, trunc=None, bv=None, boot=None, 
     the advantages whitened over the steps that take part. A zero-filled workspace for
     whitening is allocated when none is given (a workspace passed in must have been zero-filled
     before its first use)."""
+    done = (_fast or _load_fast()).gae_masked(r, v, mask, term, trunc, bv, boot, adv, ret, gamma,
+        lam, normalize, eps, want_ret, ws)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("bv", bv, N, T, dt, dev)
     _check_data("boot", boot, N, T, dt, dev, shape=(N,))
@@ -534,6 +610,10 @@ def rlcs_gae_masked_noalloc(r, v, mask=None, term=None, trunc=None, bv=None, boo
                             eps: float = 1e-8, want_ret: bool = True):
     """rlcs_gae_masked with the library's built-in whitening workspace (N <= 65536): the C call
     allocates nothing. Pass `adv` (and `ret`) to keep this wrapper from allocating them."""
+    done = (_fast or _load_fast()).gae_masked(r, v, mask, term, trunc, bv, boot, adv, ret, gamma,
+        lam, normalize, eps, want_ret)
+    if done is not NotImplemented:
+        return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("bv", bv, N, T, dt, dev)
     _check_data("boot", boot, N, T, dt, dev, shape=(N,))

@@ -5,9 +5,10 @@ Loading fails loudly when the library has not been built: there is no fallback p
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
-from .build import LIB
+from .build import BINDING_LIB, LIB
 
 RLCS_OK = 0
 RLCS_ERR_INVALID_ARG = 1
@@ -100,3 +101,24 @@ class RlcsError(RuntimeError):
     def __init__(self, fn: str, code: int):
         super().__init__(f"{fn} returned {code}: {status_string(code)}")
         self.code = code
+
+
+_binding = None
+
+
+def binding():
+    """The native side of the binding (csrc/binding.cpp), bound to librlcs.so. Raises if it has
+    not been built."""
+    global _binding
+    if _binding is None:
+        lib = load()
+        if not os.path.exists(BINDING_LIB):
+            raise RuntimeError(
+                f"{BINDING_LIB} is missing: build it first (python -m paper_2608_17641_amd.build "
+                "or __graft_entry__.build())")
+        spec = importlib.util.spec_from_file_location(__package__ + "._binding", BINDING_LIB)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(lib._handle, RlcsError)
+        _binding = module
+    return _binding

@@ -6,7 +6,9 @@ produces ``paper_2608_17641_amd/librlcs.so`` from the translation units ``csrc/r
 (one per group of entry points, compiled in parallel; kernels in ``csrc/rlcs_*.h``) against
 the public header ``include/rlcs.h``, and ``paper_2608_17641_amd/libprobe.so`` from
 ``csrc/probe_stream.hip``: reference kernels that bench.py times beside the library (a streaming
-copy with GAE's byte split, an empty launch), not part of the library.
+copy with GAE's byte split, an empty launch), not part of the library; and
+``paper_2608_17641_amd/_binding.so`` from ``csrc/binding.cpp``, the native side of the Python
+binding (host code only, g++ against PyTorch's headers).
 """
 from __future__ import annotations
 
@@ -25,6 +27,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librlcs.so")
 PROBE_LIB = os.path.join(PKG, "libprobe.so")
 PROBE_SOURCE = os.path.join(CSRC, "probe_stream.hip")
+BINDING_LIB = os.path.join(PKG, "_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 SOURCES = sorted(glob.glob(os.path.join(CSRC, "rlcs_*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "rlcs_*.h"))) + [os.path.join(INCLUDE, "rlcs.h")]
 
@@ -61,6 +65,21 @@ def link_command(objs, out: str = LIB):
     return [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out, *objs]
 
 
+def binding_command(out: str = BINDING_LIB):
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-I{INCLUDE}", f"-I{inc}", f"-I{os.path.join(inc, 'torch', 'csrc', 'api', 'include')}",
+            f"-I{sysconfig.get_paths()['include']}", "-isystem", "/opt/rocm/include",
+            "-o", out, BINDING_SOURCE, f"-L{os.path.join(root, 'lib')}",
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
@@ -78,20 +97,23 @@ def _run(cmd):
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile librlcs.so and libprobe.so: always when force, else only what does not exist
-    yet."""
-    if not force and os.path.exists(LIB) and os.path.exists(PROBE_LIB):
+    """Compile librlcs.so, libprobe.so and _binding.so: always when force, else only if one of
+    them does not exist yet."""
+    if not force and all(os.path.exists(p) for p in (LIB, PROBE_LIB, BINDING_LIB)):
         return LIB
     with tempfile.TemporaryDirectory(prefix="rlcs_build_") as tmpdir:
         objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in SOURCES]
         probe_obj = os.path.join(tmpdir, "probe_stream.o")
         jobs = min(len(SOURCES) + 1, max(1, min(8, os.cpu_count() or 1)))
-        with ThreadPoolExecutor(max_workers=jobs) as pool:
+        binding_tmp = BINDING_LIB + f".tmp{os.getpid()}"
+        with ThreadPoolExecutor(max_workers=jobs + 1) as pool:
+            binding = pool.submit(_run, binding_command(binding_tmp))
             results = list(pool.map(lambda so: (so[0], _run(compile_command(*so))),
                                     list(zip(SOURCES, objs)) + [(PROBE_SOURCE, probe_obj)]))
+            results.append((BINDING_SOURCE, binding.result()))
         for src, (rc, err) in results:
             if rc != 0:
-                raise RuntimeError(f"hipcc failed on {src} ({rc}):\n{err}")
+                raise RuntimeError(f"compiling {src} failed ({rc}):\n{err}")
             if verbose and err.strip():
                 print(err, file=sys.stderr)
         for objects, out in ((objs, LIB), ([probe_obj], PROBE_LIB)):
@@ -102,6 +124,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
                     os.remove(tmp)
                 raise RuntimeError(f"link of {os.path.basename(out)} failed ({rc}):\n{err}")
             os.replace(tmp, out)
+        os.replace(binding_tmp, BINDING_LIB)
     return LIB
 
 
