@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(kActMaxWaves * kWave) action_rows_kernel(Args 
         if (W > 1) {
             if (lane == kWave - 1) { s_a[wave] = incl.a; s_b[wave] = incl.b; }
             __syncthreads();
-            for (int j = W - 1; j > wave; --j) win = compose(Pair{s_a[j], s_b[j]}, win);
+            win = waves_in<true>(s_a, s_b, W, wave, lane);
         }
         const float Xw = apply(win, carry);
         const float X = shift_up1(apply(incl, Xw), Xw);

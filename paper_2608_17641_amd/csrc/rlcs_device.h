@@ -63,18 +63,49 @@ __device__ __forceinline__ Pair read_lane(Pair v, int lane) {
 // the row totals onto the rows after them. Twelve VALU operations, no LDS, no lane reads;
 // moving the source maps into registers first (with the identity where a source is missing)
 // and reading the row totals into scalars took 39.
-__device__ __forceinline__ Pair wave_scan_inclusive(Pair v, int lane) {
-    (void)lane;
+__device__ __forceinline__ Pair row_scan_inclusive(Pair v) {  // within each row of 16 lanes
     RLCS_DPP_STEP(v, "row_shr:1 row_mask:0xf");
     RLCS_DPP_STEP(v, "row_shr:2 row_mask:0xf");
     RLCS_DPP_STEP(v, "row_shr:4 row_mask:0xf");
     RLCS_DPP_STEP(v, "row_shr:8 row_mask:0xf");
+    return v;
+}
+__device__ __forceinline__ Pair wave_scan_inclusive(Pair v, int lane) {
+    (void)lane;
+    v = row_scan_inclusive(v);
     // rows 1 and 3 take lane 15 of the row before; then rows 2 and 3 take lane 31
     RLCS_DPP_STEP(v, "row_bcast:15 row_mask:0xa");
     RLCS_DPP_STEP(v, "row_bcast:31 row_mask:0xc");
     return v;
 }
 #undef RLCS_DPP_STEP
+
+// Composition of the maps of the waves on wave `wave`'s carry-source side (those after it for
+// backward scans, before it for forward ones), of W <= 16 waves with maps s_a[j], s_b[j] in LDS.
+// Up to eight waves compose one after the other. With more, lane i of each row of 16 takes the
+// i-th wave from the carry source (the identity past the wave's own side) and a row scan
+// composes them: the loop waits for one LDS read after another, up to fifteen of them (TD(lambda)
+// 64 x 4096, sixteen waves, 3.65 -> 3.20 us; masked GAE 1024 x 2048, eight waves, 8.8 with the loop
+// against 9.4).
+template <bool kBack>
+__device__ __forceinline__ Pair waves_in(const float* s_a, const float* s_b, int W, int wave, int lane) {
+    Pair v = identity_pair();
+    if (W > 8) {
+        const int i = lane & 15;
+        const int n = kBack ? W - 1 - wave : wave;  // waves on that side
+        if (i < n) {
+            const int j = kBack ? W - 1 - i : i;
+            v = Pair{s_a[j], s_b[j]};
+        }
+        return read_lane(row_scan_inclusive(v), 15);
+    }
+    if (kBack) {
+        for (int j = W - 1; j > wave; --j) v = compose(Pair{s_a[j], s_b[j]}, v);
+    } else {
+        for (int j = 0; j < wave; ++j) v = compose(Pair{s_a[j], s_b[j]}, v);
+    }
+    return v;
+}
 
 // ------------------------------------------------------------------ element loads / stores
 
