@@ -19,11 +19,11 @@ namespace host {
 
 // Workgroups of `kernel` (with `threads` lanes) that the current device holds at once, or 0.
 template <class Kernel>
-int64_t resident_groups(Kernel kernel, int threads) {
+int64_t resident_groups(Kernel kernel, int threads, size_t lds = 0) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess) return 0;
     return int64_t(cus) * per_cu;
 }
 

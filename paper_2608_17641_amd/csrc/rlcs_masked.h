@@ -3,17 +3,18 @@
 //
 // A masked step (an observation token) passes on both the running advantage A and the value W
 // that the preceding unmasked step sees as its successor: the value of the next unmasked step.
-// The pair (A, W) therefore obeys one backward recurrence whose per-step map is affine with an
-// upper-triangular linear part,
-//   (A, W) at t  =  [[p, q], [0, s]] (A, W) at t+1  +  (ca, cw):
 //   unmasked, continuing:  A = r - V + gamma W' + gamma lambda A',   W = V;
 //   unmasked, cut:         A = r - V + gamma * (0 | bv | boot),       W = V;
 //   masked, continuing:    A = A', W = W';
 //   masked, cut:           A = 0,  W = (0 | bv | boot);
 // where a cut is a termination (successor 0), a truncation (its continuation bv_t) or the row's
-// last step (the bootstrap). These maps compose associatively like the pairs of Eq. 2, so one
-// segmented scan over the flat [N*T] array evaluates the recurrence: each lane composes its K
-// steps, a DPP wave scan composes lanes, LDS composes waves and carries chunks.
+// last step (the bootstrap), and A', W' are those of the step after. W does not depend on A, so the
+// kernels run two scans of the pairs of Eq. 2 over the flat [N*T] array: W (a constant at every
+// step but masked continuing ones, which are the identity), then, with W' known at every step, A.
+// Each lane composes its K steps, a DPP wave scan composes lanes, LDS composes waves and carries
+// chunks. (One scan of the triangular 2 x 2 maps of (A, W), five floats each, took one barrier
+// less, but 45 vector operations a wave for its DPP steps instead of 24 and more at every
+// composition; with eight waves on a SIMD these kernels are bound by vector operations.)
 //
 // Whitening: the scan kernel also reduces the advantages of the unmasked steps of each
 // workgroup to fp64 sums (count, sum, sum of squares) and stores them as the workgroup's
@@ -30,71 +31,10 @@
 
 namespace rlcs {
 
-// (A, W) -> (p A + q W + ca, s W + cw)
-struct Tri {
-    float p, q, s, ca, cw;
-};
+// The state between two steps: the advantage, and the value of the next unmasked step.
 struct AW {
     float A, W;
 };
-
-__device__ __forceinline__ Tri identity_tri() { return Tri{1.f, 0.f, 1.f, 0.f, 0.f}; }
-
-__device__ __forceinline__ Tri compose(const Tri& o, const Tri& i) {
-    return Tri{o.p * i.p, fmaf(o.p, i.q, o.q * i.s), o.s * i.s,
-               fmaf(o.p, i.ca, fmaf(o.q, i.cw, o.ca)), fmaf(o.s, i.cw, o.cw)};
-}
-
-__device__ __forceinline__ AW apply(const Tri& m, AW x) {
-    return AW{fmaf(m.p, x.A, fmaf(m.q, x.W, m.ca)), fmaf(m.s, x.W, m.cw)};
-}
-
-__device__ __forceinline__ float readlane_f(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-__device__ __forceinline__ Tri read_lane(const Tri& v, int lane) {
-    return Tri{readlane_f(v.p, lane), readlane_f(v.q, lane), readlane_f(v.s, lane),
-               readlane_f(v.ca, lane), readlane_f(v.cw, lane)};
-}
-
-// One Kogge-Stone step on triangular maps with DPP-modified VALU operations, as for pairs
-// (wave_scan_inclusive in the device header): a lane whose DPP source exists composes its map
-// (outer) with the source's map (inner); the others are not written and keep theirs. Every
-// component of the source is read before the source lane overwrites it, so q and ca are first
-// copied: q' = q s_src + p q_src, ca' = ca + q cw_src + p ca_src, cw' = cw + s cw_src,
-// s' = s s_src, p' = p p_src, in that order.
-#define RLCS_TRI_DPP_STEP(v, CTRL)                                                            \
-    {                                                                                         \
-        float tq = v.q, tca = v.ca;                                                           \
-        asm volatile("s_nop 1\n\tv_mul_f32_dpp %1, %2, %1 " CTRL " bank_mask:0xf\n\t"         \
-                     "s_nop 1\n\tv_fmac_f32_dpp %1, %5, %0 " CTRL " bank_mask:0xf\n\t"        \
-                     "s_nop 1\n\tv_fmac_f32_dpp %3, %4, %5 " CTRL " bank_mask:0xf\n\t"        \
-                     "s_nop 1\n\tv_fmac_f32_dpp %3, %6, %0 " CTRL " bank_mask:0xf\n\t"        \
-                     "s_nop 1\n\tv_fmac_f32_dpp %4, %4, %2 " CTRL " bank_mask:0xf\n\t"        \
-                     "s_nop 1\n\tv_mul_f32_dpp %2, %2, %2 " CTRL " bank_mask:0xf\n\t"         \
-                     "s_nop 1\n\tv_mul_f32_dpp %0, %0, %0 " CTRL " bank_mask:0xf"               \
-                     : "+v"(v.p), "+v"(v.q), "+v"(v.s), "+v"(v.ca), "+v"(v.cw), "+v"(tq), "+v"(tca)); \
-    }
-
-// Inclusive prefix scan of per-lane maps over the 64 lanes, as wave_scan_inclusive for pairs:
-// four row shifts, then the row broadcasts of lanes 15 and 31.
-__device__ __forceinline__ Tri wave_scan_inclusive(Tri v, int lane) {
-    (void)lane;
-    RLCS_TRI_DPP_STEP(v, "row_shr:1 row_mask:0xf")
-    RLCS_TRI_DPP_STEP(v, "row_shr:2 row_mask:0xf")
-    RLCS_TRI_DPP_STEP(v, "row_shr:4 row_mask:0xf")
-    RLCS_TRI_DPP_STEP(v, "row_shr:8 row_mask:0xf")
-    RLCS_TRI_DPP_STEP(v, "row_bcast:15 row_mask:0xa")
-    RLCS_TRI_DPP_STEP(v, "row_bcast:31 row_mask:0xc")
-    return v;
-}
-#undef RLCS_TRI_DPP_STEP
-
-// Value of lane l-1 (lane 0 receives `fill`).
-__device__ __forceinline__ AW shift_up1(AW v, AW fill) {
-    return AW{shift_up1(v.A, fill.A), shift_up1(v.W, fill.W)};
-}
 
 // fp64 sums of the advantages of the unmasked steps of one workgroup (or of a block of
 // partials): count, sum, sum of squares.
@@ -112,18 +52,7 @@ struct MaskedArgs {
 
 constexpr int kDirectPartials = 4096;  // partials one normalize workgroup adds up itself
 
-// Map of one step.
-__device__ __forceinline__ Tri masked_gae_step(const Params& P, bool in, bool te, bool tr, bool ed,
-                                               float r, float v, float bv, float B) {
-    const bool cut = te || tr || ed;
-    const float s_cut = te ? 0.f : (tr ? bv : B);
-    if (in) {
-        const float rv = r - v;
-        return cut ? Tri{0.f, 0.f, 0.f, fmaf(P.gamma, s_cut, rv), v}
-                   : Tri{P.gamma * P.lambda, P.gamma, 0.f, rv, v};
-    }
-    return cut ? Tri{0.f, 0.f, 0.f, 0.f, s_cut} : identity_tri();
-}
+constexpr int kMaskedWaves = 16;  // most waves of a workgroup
 
 // One lane's K consecutive steps of a chunk (lane l owns the (63-l)-th group of its wave's
 // span: the carry flows from lane l-1 to lane l).
@@ -133,9 +62,10 @@ struct MaskedChunk {
     static constexpr int kWords = K * int(sizeof(DT)) / 4;
     float r[K], v[K], bv[K], B[K];
     uint32_t mk, term, trunc, edge, valid;
-    Tri m[K];
-    Tri incl;
     int64_t p0;
+    // the maps of the scan at hand (of W, then of A): the steps', and lanes 0..lane composed
+    float al[K], be[K];
+    Pair incl;
 
     // Vector loads of the lane's K steps (16-byte aligned data, T >= K, all K steps inside the
     // array; `base` a row start at or before p0), every one issued before the first use; at most
@@ -207,23 +137,55 @@ struct MaskedChunk {
         load_k<DT, K>(a.in[2], p0, valid & trunc, false, bv);
     }
 
-    // The lane's composed map (step 0 outermost) and its inclusive wave scan.
-    __device__ __forceinline__ Tri local(const Params& P, int lane) {
+    // Composes the lane's steps (step 0 outermost) and scans the wave: the wave's map in lane 63.
+    __device__ __forceinline__ Pair scan(int lane) {
+        Pair agg{al[K - 1], be[K - 1]};
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            m[k] = bit(valid, k) ? masked_gae_step(P, bit(mk, k), bit(term, k), TR && bit(trunc, k),
-                                                   bit(edge, k), r[k], v[k], bv[k], B[k])
-                                 : identity_tri();
-        Tri agg = m[K - 1];
-#pragma unroll
-        for (int k = K - 2; k >= 0; --k) agg = compose(m[k], agg);
+        for (int k = K - 2; k >= 0; --k) agg = compose(Pair{al[k], be[k]}, agg);
         incl = wave_scan_inclusive(agg, lane);
         return incl;
     }
 
-    // Outputs given Xw, the state entering the wave's span; returns the state at the lane's
-    // first step. Accumulates the advantages that take part into (n, sum, sumsq). `full`: the
-    // lane's steps are vector-aligned (stored as vectors when all of them are the lane's).
+    // What a cut step hands to the step before it.
+    __device__ __forceinline__ float cut_value(int k) const {
+        return bit(term, k) ? 0.f : (TR && bit(trunc, k) ? bv[k] : B[k]);
+    }
+    __device__ __forceinline__ uint32_t cuts() const { return term | (TR ? trunc : 0u) | edge; }
+
+    // First scan: W. `valid` steps only; the others are the identity.
+    __device__ __forceinline__ Pair values(int lane) {
+        const uint32_t cut = cuts();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool in = bit(mk, k), on = !bit(valid, k) || (!in && !bit(cut, k));
+            al[k] = on ? 0.f : (in ? v[k] : cut_value(k));
+            be[k] = on ? 1.f : 0.f;
+        }
+        return scan(lane);
+    }
+    // Second scan: A, given the W entering the wave's span. Returns W at the lane's first step in
+    // `first`.
+    __device__ __forceinline__ Pair advantages(const Params& P, float Ww, int lane, float& first) {
+        float w = shift_up1(apply(incl, Ww), Ww);  // the W entering the lane
+        const uint32_t cut = cuts();
+        const float gl = P.gamma * P.lambda;
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            const bool in = bit(mk, k), c = bit(cut, k);
+            const float next = fmaf(be[k], w, al[k]);
+            const float a = fmaf(P.gamma, c ? cut_value(k) : w, r[k] - v[k]);
+            al[k] = (in && bit(valid, k)) ? a : 0.f;
+            be[k] = bit(valid, k) ? (c ? 0.f : (in ? gl : 1.f)) : 1.f;
+            w = next;
+        }
+        first = w;
+        return scan(lane);
+    }
+
+    // Outputs given Aw, the advantage entering the wave's span; returns the advantage at the lane's
+    // first step. Accumulates the advantages that take part into the sum and sum of squares (their
+    // count is count_wave's). `full`: the lane's steps are vector-aligned (stored as vectors when
+    // all of them are the lane's).
     float adv[K];  // the lane's advantages (kept for the fused whitening)
     // K = 8: the wave's LDS slot for whole-line stores. A wave whose lanes all store whole
     // vectors holds 512 consecutive outputs (lane l the group 63 - l of them).
@@ -244,39 +206,53 @@ struct MaskedChunk {
         store_k<K>(out, p0, valid, vstore, v);
     }
 
-    template <bool STATS, bool STORE_ADV = true>
-    __device__ __forceinline__ AW finish(const Args& a, AW Xw, bool full, double& n, double& s1,
-                                         double& s2) {
-        AW x = shift_up1(apply(incl, Xw), Xw);
-        float ret[K];
+    template <bool STATS, bool STORE = true>
+    __device__ __forceinline__ float finish(const Args& a, float Aw, bool full, double& s1, double& s2) {
+        float x = shift_up1(apply(incl, Aw), Aw);
 #pragma unroll
         for (int k = K - 1; k >= 0; --k) {
-            x = apply(m[k], x);
-            adv[k] = x.A;
-            ret[k] = x.A + v[k];
-            if (STATS && bit(valid, k) && bit(mk, k)) {
-                const double d = double(x.A);
-                n += 1.0;
+            x = fmaf(be[k], x, al[k]);
+            adv[k] = x;
+            if (STATS) {
+                const double d = double(bit(valid & mk, k) ? x : 0.f);
                 s1 += d;
                 s2 = fma(d, d, s2);
             }
         }
-        const bool vstore = full && valid == kAll;
-        if (STORE_ADV) store(a.out0, vstore, adv);
-        if (a.out1) store(a.out1, vstore, ret);
+        if (STORE) {
+            store(a.out0, full && valid == kAll, adv);
+            store_returns(a, full);
+        }
         return x;
+    }
+
+    // Steps of the wave that take part (the same in every lane).
+    __device__ __forceinline__ int count_wave() const {
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) n += __popcll(__ballot(bit(valid & mk, k)));
+        return n;
+    }
+
+    // The value targets, if asked for.
+    __device__ __forceinline__ void store_returns(const Args& a, bool full) {
+        if (!a.out1) return;
+        float ret[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) ret[k] = adv[k] + v[k];
+        store(a.out1, full && valid == kAll, ret);
     }
 };
 
-// Sum over the 64 lanes in fp64, the same value in every lane, in one fixed order: a DPP
-// prefix sum inside each row of 16 lanes (both 32-bit halves moved by row shifts, zeros shifted
-// in), then the four row totals read as scalars. Against a shuffle butterfly (12 LDS-speed
-// permutes per value) this took whitened masked GAE 1024 x 2048 from 21.9 to 19.8 us.
-template <int kCtrl>
+// Sum over the 64 lanes in fp64, in lane 63, in one fixed order: a DPP prefix sum inside each row
+// of 16 lanes (both 32-bit halves moved by row shifts, zeros shifted in), then the row broadcasts
+// of lanes 15 and 31 as in the scans. Against a shuffle butterfly (12 LDS-speed permutes per value)
+// row shifts took whitened masked GAE 1024 x 2048 from 21.9 to 19.8 us.
+template <int kCtrl, int kRows = 0xf>
 __device__ __forceinline__ double dpp_move_f64(double v) {
     const uint64_t u = __double_as_longlong(v);
-    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u)), kCtrl, 0xf, 0xf, false));
-    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), kCtrl, 0xf, 0xf, false));
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u)), kCtrl, kRows, 0xf, false));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), kCtrl, kRows, 0xf, false));
     return __longlong_as_double((uint64_t(hi) << 32) | lo);
 }
 __device__ __forceinline__ double read_lane_f64(double v, int lane) {
@@ -285,12 +261,24 @@ __device__ __forceinline__ double read_lane_f64(double v, int lane) {
     const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), lane));
     return __longlong_as_double((uint64_t(hi) << 32) | lo);
 }
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
 __device__ __forceinline__ double wave_sum(double x) {
     x += dpp_move_f64<kDppRowShr + 1>(x);
     x += dpp_move_f64<kDppRowShr + 2>(x);
     x += dpp_move_f64<kDppRowShr + 4>(x);
     x += dpp_move_f64<kDppRowShr + 8>(x);
-    return (read_lane_f64(x, 15) + read_lane_f64(x, 31)) + (read_lane_f64(x, 47) + read_lane_f64(x, 63));
+    x += dpp_move_f64<kDppBcast15, 0xa>(x);
+    x += dpp_move_f64<kDppBcast31, 0xc>(x);
+    return x;
+}
+
+// Sum over the first 16 lanes, the same value in every lane (the other lanes' values are not used).
+__device__ __forceinline__ double row_sum(double x) {
+    x += dpp_move_f64<kDppRowShr + 1>(x);
+    x += dpp_move_f64<kDppRowShr + 2>(x);
+    x += dpp_move_f64<kDppRowShr + 4>(x);
+    x += dpp_move_f64<kDppRowShr + 8>(x);
+    return read_lane_f64(x, 15);
 }
 
 // Step 1 of one chunk [chunk_lo, chunk_hi) of a workgroup's range [lo, hi) (lane l of wave w
@@ -329,18 +317,19 @@ __device__ __forceinline__ void masked_chunk_load(MaskedChunk<DT, K, TR, HM>& c,
     }
 }
 
-// Rows kernel for masked GAE: workgroup g owns rows [g*R, g*R + R) and walks them in chunks of
-// E = W*64*K steps from the end. `wave_local`: every row lies within one wave's span, so no
+// Rows kernel for masked GAE: workgroup g of W = blockDim / 64 waves owns rows [g*R, g*R + R) and
+// walks them in chunks of E = W*64*K steps from the end. `wave_local`: every row lies within one wave's span, so no
 // carry crosses waves.
-template <typename DT, int K, int W, bool VEC, bool TR, bool HM, bool STATS>
-__global__ void __launch_bounds__(W * kWave) masked_gae_kernel(MaskedArgs ma, int64_t rows_per_wg,
-                                                               int wave_local) {
+template <typename DT, int K, bool VEC, bool TR, bool HM, bool STATS>
+__global__ void __launch_bounds__(kMaskedWaves * kWave) masked_gae_kernel(MaskedArgs ma, int64_t rows_per_wg,
+                                                                          int wave_local) {
     const Args& a = ma.a;
-    constexpr int64_t E = int64_t(W) * kWave * K;
-    __shared__ float s_m[5][W];
+    const int W = blockDim.x / kWave;
+    const int64_t E = int64_t(W) * kWave * K;
+    __shared__ float s_m[4][kMaskedWaves];  // the waves' maps of W and of A
     __shared__ float s_cA, s_cW;
-    __shared__ double s_stat[3][W];
-    __shared__ f32x4 s_out[K == 8 ? W : 1][K == 8 ? 2 * kWave : 1];
+    __shared__ double s_stat[3][kMaskedWaves];
+    extern __shared__ f32x4 s_out[];  // K = 8: 2 KB per wave
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t row_lo = int64_t(blockIdx.x) * rows_per_wg;
     const int64_t row_hi = min(row_lo + rows_per_wg, a.N);
@@ -348,38 +337,42 @@ __global__ void __launch_bounds__(W * kWave) masked_gae_kernel(MaskedArgs ma, in
     const bool can_full = VEC && a.T >= K;
     const RowBase base{lo, row_lo, 0};
     AW carry{0.f, 0.f};
-    double n = 0.0, s1 = 0.0, s2 = 0.0;
+    int64_t n = 0;
+    double s1 = 0.0, s2 = 0.0;
     int64_t chunk_hi = (hi + K - 1) / K * K;
     for (;;) {
         const int64_t chunk_lo = chunk_hi - E;
         MaskedChunk<DT, K, TR, HM> c;
-        c.oslot = s_out[K == 8 ? wave : 0];
+        c.oslot = s_out + wave * 2 * kWave;
         masked_chunk_load(c, ma, base, lo, hi, chunk_lo, chunk_hi, can_full, lane, wave);
-        const Tri incl = c.local(a.p, lane);
-        Tri win = identity_tri();
+        AW in = carry;  // the state entering the wave's span
+        const Pair mw = c.values(lane);
         if (!wave_local) {
-            if (lane == kWave - 1) {
-                s_m[0][wave] = incl.p; s_m[1][wave] = incl.q; s_m[2][wave] = incl.s;
-                s_m[3][wave] = incl.ca; s_m[4][wave] = incl.cw;
-            }
+            if (lane == kWave - 1) { s_m[0][wave] = mw.a; s_m[1][wave] = mw.b; }
             __syncthreads();
-            for (int w = W - 1; w > wave; --w)
-                win = compose(Tri{s_m[0][w], s_m[1][w], s_m[2][w], s_m[3][w], s_m[4][w]}, win);
+            in.W = apply(waves_in<true>(s_m[0], s_m[1], W, wave, lane), carry.W);
         }
-        const AW first = c.template finish<STATS>(a, apply(win, carry), can_full, n, s1, s2);
+        float w_first;
+        const Pair mA = c.advantages(a.p, in.W, lane, w_first);
+        if (!wave_local) {
+            if (lane == kWave - 1) { s_m[2][wave] = mA.a; s_m[3][wave] = mA.b; }
+            __syncthreads();
+            in.A = apply(waves_in<true>(s_m[2], s_m[3], W, wave, lane), carry.A);
+        }
+        const float a_first = c.template finish<STATS>(a, in.A, can_full, s1, s2);
+        if (STATS) n += c.count_wave();
         if (chunk_lo <= lo) break;
         // the next chunk (earlier in time) continues from the state at chunk_lo, held by lane
         // 63 of wave 0
-        if (threadIdx.x == kWave - 1) { s_cA = first.A; s_cW = first.W; }
+        if (threadIdx.x == kWave - 1) { s_cA = a_first; s_cW = w_first; }
         __syncthreads();
         carry = AW{s_cA, s_cW};
         chunk_hi = chunk_lo;
     }
     if constexpr (STATS) {
-        n = wave_sum(n);
         s1 = wave_sum(s1);
         s2 = wave_sum(s2);
-        if (lane == 0) { s_stat[0][wave] = n; s_stat[1][wave] = s1; s_stat[2][wave] = s2; }
+        if (lane == kWave - 1) { s_stat[0][wave] = double(n); s_stat[1][wave] = s1; s_stat[2][wave] = s2; }
         __syncthreads();
         if (threadIdx.x == 0) {
             Moments m{0.0, 0.0, 0.0, 0.0};
@@ -412,7 +405,7 @@ __device__ __forceinline__ Moments sum_partials(const Moments* part, int64_t lo,
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
     const int wave = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) { s_sum[0][wave] = n; s_sum[1][wave] = s1; s_sum[2][wave] = s2; }
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) { s_sum[0][wave] = n; s_sum[1][wave] = s1; s_sum[2][wave] = s2; }
     __syncthreads();
     Moments t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -491,18 +484,22 @@ __global__ void __launch_bounds__(kNormThreads) masked_normalize_kernel(float* a
 
 // ---------------------------------------------------------------- whitening in one pass
 // When every workgroup of a whitened call is resident on the GPU at once and holds one chunk,
-// the call runs as one kernel: each workgroup computes its advantages, stores the returns,
-// keeps the advantages in registers and publishes its fp64 moments; workgroup 0 adds them all
-// up (one record per lane, at most one per lane of its W waves) into the mean and
-// 1/sqrt(var + eps) and publishes them in kStatsCopies copies; every other workgroup waits for
-// its copy; then each whitens its advantages and stores them, once. Two round trips through
-// memory follow the last moments. The sums run in one fixed order, so results are
-// reproducible bit for bit. Every wait is for a workgroup that is already resident (the host
-// launches this form only when the whole grid fits on the GPU at once), and no atomic
-// read-modify-write is used (a counter that every workgroup increments serializes them, about
-// 17 ns each). A waiting workgroup polls one record with one lane, with pauses that grow, so
+// the call runs as one kernel: each workgroup computes its advantages, keeps them in registers
+// and publishes its fp64 moments; workgroup 0 adds them all up (one record per lane and turn) into
+// the mean and 1/sqrt(var + eps) and publishes them in kStatsCopies copies; every other
+// workgroup waits for its copy; then each whitens its advantages and stores them, once. Two round
+// trips through memory follow the last moments; the value targets are stored behind the moments,
+// where they fill that wait (stored before, they held the moments up). The sums run in one fixed
+// order, so results are reproducible bit for bit. Every wait is for a workgroup that is already
+// resident (the host launches this form only when the whole grid fits on the GPU at once), and no
+// atomic read-modify-write is used (a counter that every workgroup increments serializes them,
+// about 17 ns each). A waiting workgroup polls one record with one lane, with pauses that grow, so
 // that the waiting workgroups do not flood memory while others still stream their data (every
 // workgroup polling every record it needs slowed whole calls several times over).
+//
+// With 32 waves on a CU the vector operations count: whitened 1024 x 2048 float32 took 594 a wave
+// and 14.1 us with the triangular scan, 444 and 12.0 us now (two pair scans, counts by ballots,
+// sums by row broadcasts, returns behind the moments); 64 x 4096 10.1 -> 8.3, 4096 x 256 10.4 -> 9.0.
 //
 // Workspace of the whitening (zero-filled once before its first use; every call leaves it
 // ready for the next):
@@ -563,20 +560,20 @@ __device__ __forceinline__ void get_tagged(const uint64_t* w, uint32_t tag, doub
 }
 
 // One-pass whitened masked GAE: workgroup g owns rows [g*R, g*R + R), which fit in one chunk;
-// every workgroup of the grid (G <= W * 64 <= kFusedMaxGroups of them) is resident at once.
+// every workgroup of the grid (G <= kFusedMaxGroups of them) is resident at once.
 // `ws`: the whitening workspace.
-template <typename DT, int K, int W, bool VEC, bool TR, bool HM>
-__global__ void __launch_bounds__(W * kWave) masked_gae_fused_kernel(MaskedArgs ma, int64_t rows_per_wg,
-                                                                     int wave_local, float eps,
-                                                                     char* ws) {
-    static_assert(int64_t(W) * kWave <= kFusedMaxGroups, "one moments record per lane of workgroup 0");
+template <typename DT, int K, bool VEC, bool TR, bool HM>
+__global__ void __launch_bounds__(kMaskedWaves * kWave) masked_gae_fused_kernel(MaskedArgs ma, int64_t rows_per_wg,
+                                                                                int wave_local, float eps,
+                                                                                char* ws) {
     const Args& a = ma.a;
-    constexpr int64_t E = int64_t(W) * kWave * K;
-    __shared__ float s_m[5][W];
-    __shared__ double s_stat[3][W];
+    const int W = blockDim.x / kWave;
+    const int64_t E = int64_t(W) * kWave * K;
+    __shared__ float s_m[4][kMaskedWaves];  // the waves' maps of W and of A
+    __shared__ double s_stat[3][kMaskedWaves];
     __shared__ uint32_t s_tag;
     __shared__ float s_mean, s_rstd;
-    __shared__ f32x4 s_out[K == 8 ? W : 1][K == 8 ? 2 * kWave : 1];
+    extern __shared__ f32x4 s_out[];  // K = 8: 2 KB per wave
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t G = gridDim.x, g = blockIdx.x;
     const int64_t row_lo = g * rows_per_wg;
@@ -593,59 +590,71 @@ __global__ void __launch_bounds__(W * kWave) masked_gae_fused_kernel(MaskedArgs 
     if (threadIdx.x == 0) s_tag = 2u * (uint32_t(ld_relaxed(gen_word)) & 0x7fffffffu) + 1u;
 
     MaskedChunk<DT, K, TR, HM> c;
-    c.oslot = s_out[K == 8 ? wave : 0];
+    c.oslot = s_out + wave * 2 * kWave;
     masked_chunk_load(c, ma, base, lo, hi, chunk_lo, chunk_hi, can_full, lane, wave);
-    const Tri incl = c.local(a.p, lane);
-    Tri win = identity_tri();
+    AW in{0.f, 0.f};
+    const Pair mw = c.values(lane);
     if (!wave_local) {
-        if (lane == kWave - 1) {
-            s_m[0][wave] = incl.p; s_m[1][wave] = incl.q; s_m[2][wave] = incl.s;
-            s_m[3][wave] = incl.ca; s_m[4][wave] = incl.cw;
-        }
+        if (lane == kWave - 1) { s_m[0][wave] = mw.a; s_m[1][wave] = mw.b; }
         __syncthreads();
-        for (int w = W - 1; w > wave; --w)
-            win = compose(Tri{s_m[0][w], s_m[1][w], s_m[2][w], s_m[3][w], s_m[4][w]}, win);
+        in.W = waves_in<true>(s_m[0], s_m[1], W, wave, lane).a;
     }
-    double n = 0.0, s1 = 0.0, s2 = 0.0;
-    c.template finish<true, false>(a, apply(win, AW{0.f, 0.f}), can_full, n, s1, s2);
+    float w_first;
+    const Pair mA = c.advantages(a.p, in.W, lane, w_first);
+    if (!wave_local) {
+        if (lane == kWave - 1) { s_m[2][wave] = mA.a; s_m[3][wave] = mA.b; }
+        __syncthreads();
+        in.A = waves_in<true>(s_m[2], s_m[3], W, wave, lane).a;
+    }
+    double s1 = 0.0, s2 = 0.0;
+    c.template finish<true, false>(a, in.A, can_full, s1, s2);
 
-    // this workgroup's moments
-    n = wave_sum(n);
+    // this workgroup's moments, summed by wave 0: lane w takes wave w's
+    const int n = c.count_wave();
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
-    if (lane == 0) { s_stat[0][wave] = n; s_stat[1][wave] = s1; s_stat[2][wave] = s2; }
+    if (lane == kWave - 1) { s_stat[0][wave] = double(n); s_stat[1][wave] = s1; s_stat[2][wave] = s2; }
     __syncthreads();
     const uint32_t tag = s_tag;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (wave == 0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] = row_sum(lane < W ? s_stat[q][lane] : 0.0);
+        if (g != 0 && lane < 6) {  // lane i: word i of the record
+            const double x = lane < 2 ? v[0] : lane < 4 ? v[1] : v[2];
+            const uint64_t u = uint64_t(__double_as_longlong(x));
+            st_relaxed(rec + 6 * g + lane, uint64_t(tag) << 32 | ((lane & 1) ? u >> 32 : u & 0xffffffffu));
+        }
+    }
+    // the value targets go out behind the moments, while the statistics are on their way
+    c.store_returns(a, can_full);
     if (g != 0) {
         if (threadIdx.x == 0) {
-            Moments m{0.0, 0.0, 0.0, 0.0};
-            for (int w = 0; w < W; ++w) { m.n += s_stat[0][w]; m.s1 += s_stat[1][w]; m.s2 += s_stat[2][w]; }
-            uint64_t* mine = rec + 6 * g;
-            put_tagged(mine, m.n, tag);
-            put_tagged(mine + 2, m.s1, tag);
-            put_tagged(mine + 4, m.s2, tag);
-            double v[2];
-            get_tagged<2>(stats_rec + 16 * (g % kStatsCopies), tag, v, 2);
-            s_mean = float(v[0]);
-            s_rstd = float(v[1]);
+            double m[2];
+            get_tagged<2>(stats_rec + 16 * (g % kStatsCopies), tag, m, 2);
+            s_mean = float(m[0]);
+            s_rstd = float(m[1]);
         }
     } else {
-        // workgroup 0: every workgroup's moments (its own from LDS), one per lane
-        double v[3] = {0.0, 0.0, 0.0};
-        if (threadIdx.x == 0) {
-            for (int w = 0; w < W; ++w) { v[0] += s_stat[0][w]; v[1] += s_stat[1][w]; v[2] += s_stat[2][w]; }
-        } else if (threadIdx.x < G) {
-            get_tagged<3>(rec + 6 * int64_t(threadIdx.x), tag, v, 1);
+        // workgroup 0: every workgroup's moments (its own from above), in turns of one per lane
+        if (threadIdx.x != 0) { v[0] = v[1] = v[2] = 0.0; }
+        for (int64_t i = threadIdx.x; i < G; i += blockDim.x) {
+            if (i == 0) continue;
+            double m[3];
+            get_tagged<3>(rec + 6 * i, tag, m, 1);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) v[q] += m[q];
         }
-        __syncthreads();  // every lane of workgroup 0 has read s_stat
-        v[0] = wave_sum(v[0]);
-        v[1] = wave_sum(v[1]);
-        v[2] = wave_sum(v[2]);
-        if (lane == 0) { s_stat[0][wave] = v[0]; s_stat[1][wave] = v[1]; s_stat[2][wave] = v[2]; }
+        __syncthreads();  // wave 0 has read s_stat
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] = wave_sum(v[q]);
+        if (lane == kWave - 1) { s_stat[0][wave] = v[0]; s_stat[1][wave] = v[1]; s_stat[2][wave] = v[2]; }
         __syncthreads();
         if (wave == 0) {
-            Moments t{0.0, 0.0, 0.0, 0.0};
-            for (int w = 0; w < W; ++w) { t.n += s_stat[0][w]; t.s1 += s_stat[1][w]; t.s2 += s_stat[2][w]; }
+            Moments t;
+            t.n = row_sum(lane < W ? s_stat[0][lane] : 0.0);
+            t.s1 = row_sum(lane < W ? s_stat[1][lane] : 0.0);
+            t.s2 = row_sum(lane < W ? s_stat[2][lane] : 0.0);
             const double m = t.n > 0.0 ? t.s1 / t.n : 0.0;
             const double var = t.n > 1.0 ? fmax(t.s2 - t.s1 * m, 0.0) / (t.n - 1.0) : 0.0;
             const double r = 1.0 / sqrt(var + double(eps));

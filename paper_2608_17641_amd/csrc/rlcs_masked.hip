@@ -1,5 +1,6 @@
 // GAE with observation-skip masking and optional advantage whitening (Section 9.3; Table 1 and
 // Section 3.3.1 for the unmasked steps).
+#include <algorithm>
 #include <mutex>
 
 #include "rlcs_dispatch.h"
@@ -20,36 +21,36 @@ constexpr size_t masked_ws_need(int64_t N) {
            sizeof(Moments) * (masked_rows(N) + (masked_rows(N) + kDirectPartials - 1) / kDirectPartials);
 }
 
+// LDS for the whole-line stores of eight outputs per lane.
+template <typename DT>
+constexpr size_t masked_lds(int waves) { return Width<DT>::K == 8 ? size_t(waves) * 2048 : 0; }
+
 template <typename DT, bool VEC, bool TR, bool HM, bool STATS>
 void launch_masked(const MaskedArgs& ma, int waves, int64_t groups, int64_t rows_per_wg,
                    int wave_local, hipStream_t s) {
-    constexpr int K = Width<DT>::K;
-    if (waves == 1)
-        hipLaunchKernelGGL((masked_gae_kernel<DT, K, 1, VEC, TR, HM, STATS>),
-                           dim3(unsigned(groups)), dim3(kWave), 0, s, ma,
-                           rows_per_wg, wave_local);
-    else if (waves == kSmallWaves)
-        hipLaunchKernelGGL((masked_gae_kernel<DT, K, kSmallWaves, VEC, TR, HM, STATS>),
-                           dim3(unsigned(groups)), dim3(kSmallWaves * kWave), 0, s, ma,
-                           rows_per_wg, wave_local);
-    else
-        hipLaunchKernelGGL((masked_gae_kernel<DT, K, kLargeWaves, VEC, TR, HM, STATS>),
-                           dim3(unsigned(groups)), dim3(kLargeWaves * kWave), 0, s, ma,
-                           rows_per_wg, wave_local);
+    hipLaunchKernelGGL((masked_gae_kernel<DT, Width<DT>::K, VEC, TR, HM, STATS>), dim3(unsigned(groups)),
+                       dim3(unsigned(waves * kWave)), masked_lds<DT>(waves), s, ma, rows_per_wg, wave_local);
 }
 
-// The one-pass whitened call (16-wave workgroups) when its grid is resident at once; false
-// when it is not (the caller then runs the two-pass form).
+// The one-pass whitened call when its grid is resident at once; false when it is not (the caller
+// then runs the two-pass form).
 template <typename DT, bool VEC, bool TR, bool HM>
-bool launch_fused(const MaskedArgs& ma, int64_t groups, int64_t rows_per_wg, int wave_local,
+bool launch_fused(const MaskedArgs& ma, int waves, int64_t groups, int64_t rows_per_wg, int wave_local,
                   float eps, void* ws, hipStream_t s) {
-    constexpr int K = Width<DT>::K;
-    constexpr int W = kLargeWaves;
-    const auto kernel = masked_gae_fused_kernel<DT, K, W, VEC, TR, HM>;
-    if (groups > int64_t(W) * kWave || groups > resident_groups(kernel, W * kWave)) return false;
-    hipLaunchKernelGGL(kernel, dim3(unsigned(groups)), dim3(W * kWave), 0, s, ma, rows_per_wg,
-                       wave_local, eps, static_cast<char*>(ws));
+    const auto kernel = masked_gae_fused_kernel<DT, Width<DT>::K, VEC, TR, HM>;
+    if (groups > resident_groups(kernel, waves * kWave, masked_lds<DT>(waves))) return false;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(groups)), dim3(unsigned(waves * kWave)), masked_lds<DT>(waves), s,
+                       ma, rows_per_wg, wave_local, eps, static_cast<char*>(ws));
     return true;
+}
+
+// Waves of a workgroup that takes `steps` steps of K per lane in the fewest chunks of at most
+// kMaskedWaves waves.
+inline int balanced_waves(int64_t steps, int64_t K) {
+    const int64_t most = int64_t(kMaskedWaves) * kWave * K;
+    const int64_t chunks = (steps + most - 1) / most;
+    const int64_t span = chunks * kWave * K;
+    return int((steps + span - 1) / span);
 }
 
 template <typename DT>
@@ -62,9 +63,11 @@ rlcs_status run_masked(MaskedArgs& ma, bool normalize, float eps, void* ws, hipS
     // multi-turn 5.79 -> 5.54 us). With whitening they would quadruple the partials that every
     // normalize workgroup adds up (12.4 -> 13.6 us), so those calls keep four waves.
     const bool one_wave = !normalize && T % K == 0 && (int64_t(kWave) * K) % T == 0 && T >= 32 * K;
-    const int waves = (T <= E_small) ? (one_wave ? 1 : kSmallWaves) : kLargeWaves;
-    const int64_t E = int64_t(waves) * kWave * K;
     const int64_t slack = (T % K == 0) ? 0 : K - 1;
+    // Longer rows: one to a workgroup, in as few chunks as sixteen waves allow, of as many waves as
+    // these chunks need.
+    const int waves = (T <= E_small) ? (one_wave ? 1 : kSmallWaves) : balanced_waves(T + slack, K);
+    const int64_t E = int64_t(waves) * kWave * K;
     const int64_t rows_per_wg = (T <= E - slack) ? (E - slack) / T : 1;
     const int64_t groups = (N + rows_per_wg - 1) / rows_per_wg;
     if (groups > INT32_MAX) return RLCS_ERR_INVALID_ARG;
@@ -79,8 +82,9 @@ rlcs_status run_masked(MaskedArgs& ma, bool normalize, float eps, void* ws, hipS
         // every row in one 16-wave chunk: the one-pass form when the grid is resident at once
         const int64_t rows16 = (E_large - slack) / T;
         const int64_t groups16 = (N + rows16 - 1) / rows16;
+        const int waves16 = balanced_waves(std::min(rows16, N) * T + slack, K);
         bool fused = false;
-#define RLCS_FUSED(V, TRV, HMV) fused = launch_fused<DT, V, TRV, HMV>(ma, groups16, rows16, wave_local, eps, ws, s)
+#define RLCS_FUSED(V, TRV, HMV) fused = launch_fused<DT, V, TRV, HMV>(ma, waves16, groups16, rows16, wave_local, eps, ws, s)
 #define RLCS_FUSED_HM(V, TRV) \
     if (hm) { RLCS_FUSED(V, TRV, true); } else { RLCS_FUSED(V, TRV, false); }
 #define RLCS_FUSED_TR(V) \
