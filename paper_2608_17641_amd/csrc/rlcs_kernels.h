@@ -852,7 +852,13 @@ __global__ void __launch_bounds__(W * kWave) flat_rows_kernel(Args a, int R, uin
 // steps one by one. A lane's first step in the range is o steps from lo; its row is
 // floor(o * magic / 2^22) (flat_rows_kernel), taken for R > 1 only, with o < 1024 (float32) or
 // 2048 (bfloat16); with R = 1, magic is 0. T >= K: at most one row edge among a lane's steps.
-template <class Op, typename DT, int K, bool TR>
+//
+// GAPS: rows a.period > T steps apart, whose gaps are neither read nor written. Here every row
+// takes LR = ceil(T / K) lanes (`grid`) from its own first step on; where T is not a multiple of K
+// its last lane's vector is moved back onto the row's last K steps, and the steps it shares with the
+// lane before it are that lane's. A lane's row is floor(i * magic / 2^22), i < 256 its place in the
+// workgroup (0 with R = 1).
+template <class Op, typename DT, int K, bool TR, bool GAPS>
 __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args a, int R, uint32_t magic, int grid) {
     constexpr bool kBack = Op::kBackward;
     constexpr int NS = Op::kSlots;
@@ -866,13 +872,32 @@ __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args 
     const int64_t row0 = int64_t(blockIdx.x) * R;
     const int64_t lo = row0 * T;
     const int64_t hi = min(row0 + R, a.N) * T;
-    const int64_t base = lo & -int64_t(grid);
     const int g = lane_group<kBack>(lane);
-    const int64_t p0 = base + (wave * kWave + g) * K;
-    const int k_lo = p0 < lo ? int(min(lo - p0, int64_t(K))) : 0;       // the lane's steps in the
-    const int k_hi = p0 < hi ? int(min(hi - p0, int64_t(K))) : 0;       // range: [k_lo, k_hi)
-    const uint32_t valid = k_lo < k_hi ? (kAll >> (K - k_hi)) & (kAll << k_lo) : 0u;
-    const bool live = valid != 0, whole = live && p0 + K <= total;
+    // the lane's steps: p0 + k is step t + k - k_lo of row row0 + r_in for k from k_lo on, the
+    // steps of `valid` are the lane's
+    int64_t base = 0, p0;
+    uint32_t valid;
+    int k_lo, r_in, t;
+    bool next_moved = false;  // the lane after this one holds a moved vector
+    if constexpr (GAPS) {
+        const int i = wave * kWave + g, LR = grid;
+        r_in = int((uint32_t(i) * magic) >> flat_shift(4));
+        const int q = i - r_in * LR;
+        const bool mine = r_in < R && row0 + r_in < a.N && q < LR;
+        t = q * K;
+        k_lo = max(t + K - int(T), 0);
+        valid = mine ? (kAll << k_lo) & kAll : 0u;
+        p0 = (row0 + r_in) * a.period + (t - k_lo);
+        next_moved = int(T) % K != 0 && q == LR - 2;
+    } else {
+        base = lo & -int64_t(grid);
+        p0 = base + (wave * kWave + g) * K;
+        k_lo = p0 < lo ? int(min(lo - p0, int64_t(K))) : 0;            // the lane's steps in the
+        const int k_hi = p0 < hi ? int(min(hi - p0, int64_t(K))) : 0;  // range: [k_lo, k_hi)
+        valid = k_lo < k_hi ? (kAll >> (K - k_hi)) & (kAll << k_lo) : 0u;
+        r_in = t = 0;  // found while the loads are in flight
+    }
+    const bool live = valid != 0, whole = live && (GAPS || p0 + K <= total);
 
     uint32_t tw[(K + 3) / 4] = {}, rw[(K + 3) / 4] = {};
     uint32_t w[NS][kWords] = {};
@@ -895,25 +920,35 @@ __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args 
                 if (Op::slot_used(s, TR) && s != kTS) put_element(w[s], k, static_cast<const DT*>(a.in[s])[p0 + k]);
         }
     }
-    // lane 0: the step past its carry-source edge, from memory (used unless a row edge comes
-    // first; an address outside the range is replaced by one of the lane's own steps)
-    if constexpr (Op::kNbr > 0) {
-        const int64_t pn = kBack ? p0 + K : p0 - 1;
-        if (lane == 0 && live) Op::template nbr_load_raw<DT>(a, pn >= lo && pn < hi ? pn : p0 + k_lo, nraw);
+    if constexpr (!GAPS) {
+        const int o = int(p0 - lo) + k_lo;  // the lane's first step in the range, from lo
+        r_in = int((uint32_t(o) * magic) >> flat_shift(4));
+        t = o - r_in * int(T);
     }
     // the row edge among the lane's steps, if any: backward the last step of its first row,
     // forward the first step of a row
-    const int o = int(p0 - lo) + k_lo;  // the lane's first step in the range, from lo
-    const int r_in = int((uint32_t(o) * magic) >> flat_shift(4));
-    const int t = o - r_in * int(T);
-    int ke = -1;
+    int ke;
     if (kBack) ke = k_lo + int(T) - 1 - t;
+    else if (GAPS) ke = t == 0 ? k_lo : K;
     else ke = t == 0 ? k_lo : k_lo + int(T) - t;
+    // lane 0, and backward the lane before a moved vector (whose first step is another): the step
+    // past the lane's carry-source edge, from memory (used unless a row edge comes first; an
+    // address outside the row or range is replaced by one of the lane's own steps)
+    const bool from_memory = lane == 0 || (kBack && next_moved);
+    if constexpr (Op::kNbr > 0) {
+        const int64_t pn = kBack ? p0 + K : p0 - 1;
+        bool in;
+        if constexpr (GAPS) in = kBack ? t - k_lo + K < int(T) : t > k_lo;
+        else in = pn >= lo && pn < hi;
+        if (from_memory && live) Op::template nbr_load_raw<DT>(a, in ? pn : p0 + k_lo, nraw);
+    }
     const uint32_t edge = (live && ke < K) ? (1u << ke) & valid : 0u;
     const int64_t row_e = row0 + r_in + ((!kBack && ke > k_lo) ? 1 : 0);
     const bool has_rv = Op::kRowValue && a.row_value;
     const float rv = (has_rv && edge) ? load_one<DT>(a.row_value, row_e) : 0.f;
-    const uint32_t trunc = (Op::kFlags && TR) ? flag_mask<K>(rw) & valid : 0u;
+    // (flags of a moved vector's dropped steps stay: forward, they precede the lane's own)
+    const uint32_t keep = GAPS && live ? kAll : valid;
+    const uint32_t trunc = (Op::kFlags && TR) ? flag_mask<K>(rw) & keep : 0u;
     if constexpr (kTS >= 0) {
         if (trunc) {
             if (whole) {
@@ -934,7 +969,7 @@ __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args 
             for (int k = 0; k < K; ++k) d[s][k] = 0.f;
         }
     }
-    const uint32_t term = (Op::kFlags && a.term) ? flag_mask<K>(tw) & valid : 0u;
+    const uint32_t term = (Op::kFlags && a.term) ? flag_mask<K>(tw) & keep : 0u;
     float B[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) B[k] = bit(edge, k) ? rv : 0.f;
@@ -946,7 +981,7 @@ __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args 
         Op::template nbr_export<K>(a.p, d, term | trunc, own);
 #pragma unroll
         for (int i = 0; i < NB; ++i) nb[i] = shift_up1(own[i], 0.f);
-        if (lane == 0 && live && !(edge & (kBack ? (1u << (K - 1)) : 1u))) Op::nbr_fix(a, nraw, nb);
+        if (from_memory && live && !(edge & (kBack ? (1u << (K - 1)) : 1u))) Op::nbr_fix(a, nraw, nb);
     } else {
 #pragma unroll
         for (int i = 0; i < NB; ++i) nb[i] = 0.f;
@@ -986,15 +1021,24 @@ __global__ void __launch_bounds__(kRaggedWaves * kWave) ragged_rows_kernel(Args 
     }
     float o0[K], o1[K];
     Op::template finish<K, TR>(a.p, d, term, trunc, edge, B, nb, A, X, o0, o1);
-    if constexpr (K == 8) {
+    if constexpr (K == 8 && !GAPS) {
         extern __shared__ f32x4 s_out[];  // 2 KB per wave
         const int64_t wbase = base + int64_t(wave) * kWave * K;
         f32x4* slot = s_out + wave * 2 * kWave;
         store8_lines_any(a.out0, wbase, lo, hi, g, lane, o0, slot);
         if (a.out1) store8_lines_any(a.out1, wbase, lo, hi, g, lane, o1, slot);
     } else if (valid == kAll) {
-        store4_any(a.out0 + p0, f32x4{o0[0], o0[1], o0[2], o0[3]});
-        if (a.out1) store4_any(a.out1 + p0, f32x4{o1[0], o1[1], o1[2], o1[3]});
+#pragma unroll
+        for (int i = 0; i < K; i += 4) {
+            const f32x4 x0{o0[i], o0[i + 1], o0[i + 2], o0[i + 3]}, x1{o1[i], o1[i + 1], o1[i + 2], o1[i + 3]};
+            if constexpr (K == 4) {
+                store4_any(a.out0 + p0, x0);
+                if (a.out1) store4_any(a.out1 + p0, x1);
+            } else {  // two halves of a lane's outputs: plain stores, which L2 merges
+                *reinterpret_cast<f32x4_any*>(a.out0 + p0 + i) = x0;
+                if (a.out1) *reinterpret_cast<f32x4_any*>(a.out1 + p0 + i) = x1;
+            }
+        }
     } else if (live) {
         store_k<K>(a.out0, p0, valid, false, o0);
         if (a.out1) store_k<K>(a.out1, p0, valid, false, o1);
