@@ -204,11 +204,28 @@ void col_launch(const Args& a, const ColGeom& g, bool split, int64_t blocks, hip
     col_launch_nt<Op, DT, TR, true>(a, g, split, blocks, s);
 }
 
-// Columns from which the automatic choice walks them four to a lane: enough 4 * LC-column blocks to
-// fill the chip without splitting time. Below (time-major GAE float32 T x N = 256 x 4096 6.1 us on
-// narrow groups against 6.9, TD(lambda) 1000 x 4000 19.0 split against 23.1) the other column
-// kernels win.
+// Columns from which the automatic choice walks them four to a lane whatever their length: enough
+// 4 * LC-column blocks to fill the chip without splitting time. Below, only columns of one chunk
+// (colvec_short_columns): longer ones are faster split (TD(lambda) T x N = 1000 x 4000 19.0 us
+// against 23.1).
 constexpr int64_t kColVecMin = 8192;
+
+// Columns of one chunk of 16-column blocks (8 waves of 16 lane groups, 512 steps), where one pass
+// without look-back replaces split tiles. From 64 blocks (1024 columns); device times, T x N,
+// split -> here. Up to 256 steps where vectors stay aligned: float32 GAE 128 x 1024 5.1 -> 4.3 us,
+// 200 x 2048 6.9 -> 5.0; bfloat16 GAE 64 x 1500 7.5 -> 4.8, V-Trace 200 x 7000 13.7 -> 11.3,
+// Retrace 128 x 6000 10.1 -> 8.1. Not float32 from 4096 columns, where the narrow groups apply (GAE
+// 64 x 5000 4.5 us against 5.0), nor of at most 32 steps, one chunk there (20 x 4096 3.5 against
+// 4.2). Longer columns only while the blocks are one per CU, and start on 16 elements of a row, so
+// that none shares a line's half with its neighbour: 512 x 1024 GAE 8.4 -> 6.3, 512 x 4096 Retrace
+// 17.5 -> 12.2, bfloat16 V-Trace 13.4 -> 10.9, against 500 x 3001 11.9 -> 15.8 and 400 x 7000
+// 19.9 -> 21.5.
+constexpr int64_t kColVecShortMin = 1024;
+inline bool colvec_short_columns(const ColGeom& g, int64_t T, bool f32) {
+    if (!g.fcol || g.J < kColVecShortMin || T > 512) return false;
+    if (T > 256) return g.J <= 4096 && g.st % 16 == 0;
+    return g.st % kCvV == 0 && !(f32 && (T <= 32 || g.J >= 4096));
+}
 
 // Lanes side by side of cols_vec_kernel, or 0 where it does not apply (columns not adjacent, or a
 // batch row's not a multiple of four).
@@ -227,9 +244,10 @@ constexpr int64_t kColVecMin = 8192;
 //   1000 x 200 x 100 42.3 with 16 (44.6), bfloat16 500 x 256 x 256 32.6 with 16 (47); of features
 //   that do not fill lines only in many columns (100 x 1000 x 100 25.6 us split, 32.3 here).
 inline int colvec_lanes(const ColGeom& g, int64_t T, rlcs_dtype dtype) {
-    if (g.J < kColVecMin || g.J > int64_t(INT32_MAX)) return 0;
+    if (g.J > int64_t(INT32_MAX)) return 0;
     if (g.fcol ? (g.C != 1 || g.bstride != 1) : g.C % kCvV != 0) return 0;
     const bool f32 = dtype == RLCS_F32;
+    if (g.J < kColVecMin) return colvec_short_columns(g, T, f32) ? 4 : 0;
     const bool lines = g.st * int64_t(dtype_size(dtype)) % 128 == 0;
     if (!g.fcol) return g.J >= 32768 ? 16 : lines ? 8 : 0;
     if (f32 && T <= 32) return 0;

@@ -322,7 +322,8 @@ void launch(const Args& a, const ColGeom& g, hipStream_t s) {
 
 template <class Op, typename DT, bool TR, bool FCOL>
 void launch_lc(const Args& a, const ColGeom& g, int lc, hipStream_t s) {
-    if (lc == 8) launch<Op, DT, TR, FCOL, 8>(a, g, s);
+    if (lc == 4) launch<Op, DT, TR, FCOL, 4>(a, g, s);
+    else if (lc == 8) launch<Op, DT, TR, FCOL, 8>(a, g, s);
     else if (lc == 16) launch<Op, DT, TR, FCOL, 16>(a, g, s);
     else launch<Op, DT, TR, FCOL, 32>(a, g, s);
 }

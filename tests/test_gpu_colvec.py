@@ -1,5 +1,5 @@
 """Column walks with four columns to a lane (csrc/rlcs_colvec.h): time-major buffers of 8192 columns
-and more, and vector traces, on the GPU against the oracle on sampled columns (the first and last
+and more, or of 1024 and more short ones, and vector traces, on the GPU against the oracle on sampled columns (the first and last
 ones among them), at the edges of the kernel's blocks and chunks: column counts that are not a
 multiple of four, rows on and off a 128-byte line, one chunk and several, strides past the last
 column with the gap left alone, flags missing. One block width against another is the same
@@ -35,7 +35,8 @@ def _close(got, ref):
 @pytest.mark.parametrize("N,T,pad", [
     (8192, 33, 0), (8192, 257, 0), (8195, 40, 0), (8193, 129, 7), (9001, 127, 0), (9002, 130, 62),
     (16384, 65, 0), (16387, 128, 0), (24576, 193, 0), (24577, 200, 0), (24579, 260, 1), (49153, 34, 0),
-    (49152, 50, 0)])
+    (49152, 50, 0), (1024, 33, 0), (1024, 512, 0), (1027, 256, 1), (1030, 257, 10), (2049, 31, 3),
+    (4095, 255, 1), (4093, 511, 3), (4096, 512, 0), (4100, 64, 0), (8188, 16, 0)])
 def test_time_major(N, T, pad, dtype):
     ro = workloads.make_rollout(N, T, seed=N + T, dtype=dtype, p_term=0.03, p_trunc=0.03)
     ld = N + pad
