@@ -341,12 +341,26 @@ rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, boo
     auto run = [&](auto dt_tag) -> rlcs_status {
         using DT = decltype(dt_tag);
         constexpr int K = Width<DT>::K;
+        // Whole vectors throughout: T >= K, data and outputs 16-byte aligned, flags K-byte aligned.
+        bool vec = a.T >= K;
+        for (int i = 0; i < Op::kSlots; ++i)
+            if (Op::slot_used(i, has_trunc) && !aligned(a.in[i], 16)) vec = false;
+        if (!aligned(a.out0, 16) || (a.out1 && !aligned(a.out1, 16))) vec = false;
+        if (Op::kFlags && ((a.term && !aligned(a.term, K)) || (has_trunc && !aligned(a.trunc, K)))) vec = false;
+        const int64_t E_small = int64_t(kSmallWaves) * kWave * K;
         // Rows of one vector to sixteen waves: each row's lanes from its own first step on. As many
         // rows as four waves hold, or one on as many waves as it needs. Against the lane-by-lane
         // rows kernel: V-Trace bfloat16 13064 x 64 (stride 68) 14.5 -> 6.1 us, eligibility traces
         // 32523 x 907 (911) 124 -> 49, GAE float32 5038 x 483 (491) 17.7 -> 11.1.
+        // Not bfloat16 rows of whole aligned vectors (32 to 2048 steps) that do not tile a wave of 128
+        // steps or more: the rows kernel's one load per vector is faster there (V-Trace 8192 x 200
+        // (256) 6.9 us against 8.8, GAE 6000 x 768 (832) 14.0 against 15.5, 2500 x 2000 (2048) 14.6
+        // against 15.9, eligibility traces 9.1 against 10.6), while 8192 x 512 (576) 13.2 us and
+        // 16000 x 128 (192) 8.4 gain from 13.7 and 9.3 here.
         const int64_t LR = (a.T + K - 1) / K;
-        if (g_variant == 0 && a.T >= K && LR <= kRaggedWaves * kWave) {
+        const bool whole = vec && sizeof(DT) == 2 && a.T % K == 0 && period % K == 0 && a.T >= 32 &&
+                           a.T <= E_small && (a.T < 128 || kWave * K % a.T != 0);
+        if (g_variant == 0 && !whole && a.T >= K && LR <= kRaggedWaves * kWave) {
             const int64_t R = LR <= kSmallWaves * kWave ? kSmallWaves * kWave / LR : 1;
             const int64_t groups = (a.N + R - 1) / R;
             if (groups > INT32_MAX) return RLCS_ERR_INVALID_ARG;
@@ -360,7 +374,6 @@ rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, boo
         }
         Plan p{};
         p.split = false;
-        const int64_t E_small = int64_t(kSmallWaves) * kWave * K;
         p.waves = (a.T <= E_small) ? kSmallWaves : kLargeWaves;
         const int64_t E = int64_t(p.waves) * kWave * K;
         const int64_t slack = (period % K == 0) ? 0 : K - 1;
@@ -372,12 +385,7 @@ rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, boo
         p.flat_R = 0;
         p.flat_W = kSmallWaves;
         // Vector path, lane by lane (lanes whose steps reach into a gap or past the range go
-        // element-wise): T >= K, data and outputs 16-byte aligned, flags K-byte aligned.
-        bool vec = a.T >= K;
-        for (int i = 0; i < Op::kSlots; ++i)
-            if (Op::slot_used(i, has_trunc) && !aligned(a.in[i], 16)) vec = false;
-        if (!aligned(a.out0, 16) || (a.out1 && !aligned(a.out1, 16))) vec = false;
-        if (Op::kFlags && ((a.term && !aligned(a.term, K)) || (has_trunc && !aligned(a.trunc, K)))) vec = false;
+        // element-wise).
         p.pad = vec;
         auto go = [&](auto tr_tag) -> rlcs_status {
             constexpr bool TR = decltype(tr_tag)::value;
