@@ -222,8 +222,10 @@ size_t rlcs_workspace_size(int64_t N, int64_t T);
  *            normalize = 0.
  * Rows are never split across workgroups for this entry point. A whitened call whose rows fit
  * in one workgroup's chunk (T <= 4096 float32 / 8192 bfloat16 steps) and whose workgroups
- * are all resident on the GPU at once runs as one kernel that reads and writes every array
- * once; otherwise a second kernel rewrites the advantages.                                  */
+ * are all resident on an idle GPU at once runs as one kernel that reads and writes every array
+ * once; otherwise a second kernel rewrites the advantages. Calls with workspaces of their own may
+ * overlap on one GPU (on other streams): where their workgroups do not all fit, some of the
+ * advantages are written twice, with the same results. */
 rlcs_status rlcs_gae_masked(const void* r, const void* v, const uint8_t* mask,
                             const uint8_t* term, const uint8_t* trunc, const void* bv,
                             const void* boot, float* adv, float* ret, int64_t N, int64_t T,

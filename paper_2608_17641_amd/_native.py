@@ -68,6 +68,7 @@ PROTOTYPES = {
     "rlcs_status_string": [_INT],
     "rlcs_version": [],
     "rlcs_testing_set_variant": [_INT],
+    "rlcs_testing_set_whitening_wait": [_INT],
 }
 RESTYPES = {"rlcs_workspace_size": _SZ, "rlcs_workspace_size_columns": _SZ,
             "rlcs_workspace_size_masked": _SZ,

@@ -9,6 +9,7 @@ using namespace rlcs::host;
 namespace rlcs {
 namespace host {
 thread_local int g_variant = 0;
+thread_local int g_whitening_wait = -1;
 }  // namespace host
 }  // namespace rlcs
 
@@ -39,6 +40,12 @@ int rlcs_version(void) { return 100; }
 rlcs_status rlcs_testing_set_variant(int variant) {
     if (variant < 0 || variant > 4) return RLCS_ERR_INVALID_ARG;
     g_variant = variant;
+    return RLCS_OK;
+}
+
+rlcs_status rlcs_testing_set_whitening_wait(int polls) {
+    if (polls < -1) return RLCS_ERR_INVALID_ARG;
+    g_whitening_wait = polls;
     return RLCS_OK;
 }
 

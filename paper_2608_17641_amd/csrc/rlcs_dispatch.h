@@ -69,6 +69,7 @@ constexpr int64_t kMaxT = int64_t(1) << 30;
 // Kernel-variant override of the calling thread (rlcs_testing_set_variant, a test-only entry
 // point); defined in rlcs_common.hip.
 extern thread_local int g_variant;
+extern thread_local int g_whitening_wait;  // rlcs_testing_set_whitening_wait; -1: as ever
 
 inline bool aligned(const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
 inline bool unit_interval(float x) { return x >= 0.f && x <= 1.f; }  // false for NaN

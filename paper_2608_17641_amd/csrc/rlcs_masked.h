@@ -27,6 +27,8 @@
 // when |mean| / std approaches 1e6, far past what fp32 advantages resolve anyway.
 #pragma once
 
+#include <stddef.h>
+
 #include "rlcs_kernels.h"
 
 namespace rlcs {
@@ -490,12 +492,24 @@ __global__ void __launch_bounds__(kNormThreads) masked_normalize_kernel(float* a
 // workgroup waits for its copy; then each whitens its advantages and stores them, once. Two round
 // trips through memory follow the last moments; the value targets are stored behind the moments,
 // where they fill that wait (stored before, they held the moments up). The sums run in one fixed
-// order, so results are reproducible bit for bit. Every wait is for a workgroup that is already
-// resident (the host launches this form only when the whole grid fits on the GPU at once), and no
-// atomic read-modify-write is used (a counter that every workgroup increments serializes them,
-// about 17 ns each). A waiting workgroup polls one record with one lane, with pauses that grow, so
+// order, so results are reproducible bit for bit. No atomic read-modify-write is on that way
+// (a counter that every workgroup increments serializes them, about 17 ns each). A waiting
+// workgroup polls one record with one lane, with pauses that grow, so
 // that the waiting workgroups do not flood memory while others still stream their data (every
 // workgroup polling every record it needs slowed whole calls several times over).
+//
+// No wait needs the whole grid resident, which the host can ask of an idle GPU only: two such calls
+// on two streams may each hold a part of it. A workgroup other than 0 that has polled kWaitPolls
+// times (some 0.1 ms) stores its advantages as they are and leaves, which makes room for those
+// still to start; workgroup 0 alone waits on, and whitens what the others left behind once it has
+// the statistics. Who whitens is settled by exchanges on two words:
+//   a leaver puts kLeft in its hand word behind its stores and counts itself in the call's word;
+//   workgroup 0, with the statistics out, closes the call's word (its tag, no leavers) and, if it
+//     held leavers, puts kClosed in every hand word: those that held kLeft are its own to whiten;
+//   a leaver that finds the call closed takes its hand back: it whitens for itself unless it finds
+//     kClosed there in place of its kLeft.
+// A call that nobody leaves pays one atomic of workgroup 0 (kClosed in every hand word each time
+// took 1024 x 2048 float32 from 12.0 to 12.5 us).
 //
 // With 32 waves on a CU the vector operations count: whitened 1024 x 2048 float32 took 594 a wave
 // and 14.1 us with the triangular scan, 444 and 12.0 us now (two pair scans, counts by ballots,
@@ -507,21 +521,44 @@ __global__ void __launch_bounds__(kNormThreads) masked_normalize_kernel(float* a
 //   [16, 24)   generation: the number of one-pass calls made on the workspace (mod 2^31);
 //              workgroup 0 advances it once every moment of its call is in, hence after every
 //              workgroup of the call has read it;
+//   [24, 32)   the call's word: the tag of the last call that closed << 32 | leavers since;
 //   kMaskedFusedOff: one tagged moments record (six words) per workgroup, kFusedMaxGroups;
 //   kMaskedStatsOff: kStatsCopies copies of the tagged statistics record (four words), one per
 //              128-byte line;
-//   kMaskedTwoPassOff: the partials of the two-pass form (Moments, 32 bytes each).
+//   kMaskedTwoPassOff: the partials of the two-pass form (Moments, 32 bytes each), whose last
+//              word is workgroup g's hand in the one-pass form: kLeft, kClosed or kTaken with its
+//              call's tag (the two-pass form leaves 0 there, which no tag equals).
 // A tagged word holds a 32-bit half of a double in its low half and the tag 2*gen + 1 of its
 // call in the high half; a reader takes a double only when both of its words carry the
 // current tag, so no word of another call (or of the two-pass partials, which live apart)
-// passes for a current one. Polls are bounded (the loads may see a write late); on exhaustion
-// the statistics are NaN.
+// passes for a current one. Workgroup 0's polls are bounded as well (about a second); on
+// exhaustion the statistics are NaN.
 constexpr int64_t kFusedMaxGroups = 1024;
 constexpr int kStatsCopies = 64;
 constexpr size_t kMaskedGenOff = 16;
+constexpr size_t kMaskedCloseOff = 24;
 constexpr size_t kMaskedFusedOff = 64;
 constexpr size_t kMaskedStatsOff = (kMaskedFusedOff + 48 * size_t(kFusedMaxGroups) + 127) / 128 * 128;
 constexpr size_t kMaskedTwoPassOff = kMaskedStatsOff + 128 * size_t(kStatsCopies);
+constexpr uint32_t kWaitPolls = 256;
+constexpr uint64_t kLeft = uint64_t(1) << 32, kClosed = uint64_t(2) << 32, kTaken = uint64_t(3) << 32;
+
+__device__ __forceinline__ uint64_t* hand_word(char* ws, int64_t g) {
+    return reinterpret_cast<uint64_t*>(ws + kMaskedTwoPassOff + sizeof(Moments) * size_t(g) + offsetof(Moments, pad));
+}
+// Puts `v` there and says what was there before. Relaxed: whoever leaves has fenced its stores, and
+// workgroup 0 fences where it finds that someone has (a fence writes back or drops cache lines).
+__device__ __forceinline__ uint64_t exchange(uint64_t* word, uint64_t v) {
+    return __hip_atomic_exchange(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// One lane of a workgroup whose advantages are stored and fenced: whether workgroup 0 whitens them.
+__device__ __forceinline__ bool leave(char* ws, int64_t g, uint32_t tag) {
+    uint64_t* hand = hand_word(ws, g);
+    if (exchange(hand, kLeft | tag) == (kClosed | tag)) return false;
+    const uint64_t old = __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(ws + kMaskedCloseOff), uint64_t(1),
+                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return uint32_t(old >> 32) != tag || exchange(hand, kTaken | tag) == (kClosed | tag);
+}
 
 __device__ __forceinline__ void put_tagged(uint64_t* w, double v, uint32_t tag) {
     const uint64_t u = uint64_t(__double_as_longlong(v));
@@ -531,9 +568,9 @@ __device__ __forceinline__ void put_tagged(uint64_t* w, double v, uint32_t tag) 
 
 // Doubles v[0 .. M) from the tagged words w[0 .. 2M) once every word carries `tag`: all words
 // are loaded at once and reloaded until they do, after a pause that doubles from `pause`
-// to about 500 cycles (NaN after kMaxPolls rounds).
+// to about 500 cycles. False, and NaN, after `most` rounds.
 template <int M>
-__device__ __forceinline__ void get_tagged(const uint64_t* w, uint32_t tag, double (&v)[M], int pause) {
+__device__ __forceinline__ bool get_tagged(const uint64_t* w, uint32_t tag, double (&v)[M], int pause, uint32_t most) {
     uint64_t x[2 * M];
 #pragma unroll
     for (int i = 0; i < 2 * M; ++i) x[i] = ld_relaxed(w + i);
@@ -542,10 +579,10 @@ __device__ __forceinline__ void get_tagged(const uint64_t* w, uint32_t tag, doub
 #pragma unroll
         for (int i = 0; i < 2 * M; ++i) ok = ok && uint32_t(x[i] >> 32) == tag;
         if (ok) break;
-        if (polls >= kMaxPolls) {
+        if (polls >= most) {
 #pragma unroll
             for (int i = 0; i < M; ++i) v[i] = __builtin_nan("");
-            return;
+            return false;
         }
         for (int i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(2);
         pause = min(2 * pause, 4);
@@ -557,21 +594,47 @@ __device__ __forceinline__ void get_tagged(const uint64_t* w, uint32_t tag, doub
 #pragma unroll
     for (int i = 0; i < M; ++i)
         v[i] = __longlong_as_double(int64_t((x[2 * i + 1] << 32) | (x[2 * i] & 0xffffffffu)));
+    return true;
 }
 
-// One-pass whitened masked GAE: workgroup g owns rows [g*R, g*R + R), which fit in one chunk;
-// every workgroup of the grid (G <= kFusedMaxGroups of them) is resident at once.
-// `ws`: the whitening workspace.
+// Workgroup 0 of a call that some of the G - 1 others have left: takes their hands and whitens the
+// advantages of those that left (R rows of T steps each, N rows in all). Every lane takes part.
+__device__ __forceinline__ void whiten_left(char* ws, uint32_t tag, int64_t G, float* adv, int64_t R, int64_t N,
+                                            int64_t T, float mean, float rstd) {
+    __shared__ uint64_t s_left[kMaskedWaves];
+    const int W = blockDim.x / kWave;
+    for (int64_t g0 = 0; g0 < G; g0 += blockDim.x) {
+        const int64_t g = g0 + threadIdx.x;
+        const bool left = g > 0 && g < G && exchange(hand_word(ws, g), kClosed | tag) == (kLeft | tag);
+        const uint64_t mask = __ballot(left);
+        if ((threadIdx.x & (kWave - 1)) == 0) s_left[threadIdx.x / kWave] = mask;
+        __syncthreads();
+        __threadfence();
+        for (int w = 0; w < W; ++w) {
+            for (uint64_t m = s_left[w]; m; m &= m - 1) {
+                const int64_t row = (g0 + w * kWave + __builtin_ctzll(m)) * R;
+                const int64_t end = min(row + R, N) * T;
+                for (int64_t p = row * T + threadIdx.x; p < end; p += blockDim.x) adv[p] = (adv[p] - mean) * rstd;
+            }
+        }
+        __syncthreads();  // s_left has been read
+    }
+}
+
+// One-pass whitened masked GAE: workgroup g of the G <= kFusedMaxGroups owns rows [g*R, g*R + R),
+// which fit in one chunk. `ws`: the whitening workspace; `wait`: polls before a workgroup leaves.
 template <typename DT, int K, bool VEC, bool TR, bool HM>
 __global__ void __launch_bounds__(kMaskedWaves * kWave) masked_gae_fused_kernel(MaskedArgs ma, int64_t rows_per_wg,
                                                                                 int wave_local, float eps,
-                                                                                char* ws) {
+                                                                                char* ws, uint32_t wait) {
     const Args& a = ma.a;
     const int W = blockDim.x / kWave;
     const int64_t E = int64_t(W) * kWave * K;
     __shared__ float s_m[4][kMaskedWaves];  // the waves' maps of W and of A
     __shared__ double s_stat[3][kMaskedWaves];
     __shared__ uint32_t s_tag;
+    __shared__ bool s_have;  // the workgroup has the statistics
+    __shared__ uint32_t s_leavers;
     __shared__ float s_mean, s_rstd;
     extern __shared__ f32x4 s_out[];  // K = 8: 2 KB per wave
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -628,20 +691,21 @@ __global__ void __launch_bounds__(kMaskedWaves * kWave) masked_gae_fused_kernel(
     }
     // the value targets go out behind the moments, while the statistics are on their way
     c.store_returns(a, can_full);
+    auto wait_stats = [&](uint32_t most) {  // one lane
+        double m[2];
+        s_have = get_tagged<2>(stats_rec + 16 * (g % kStatsCopies), tag, m, 2, most);
+        s_mean = float(m[0]);
+        s_rstd = float(m[1]);
+    };
     if (g != 0) {
-        if (threadIdx.x == 0) {
-            double m[2];
-            get_tagged<2>(stats_rec + 16 * (g % kStatsCopies), tag, m, 2);
-            s_mean = float(m[0]);
-            s_rstd = float(m[1]);
-        }
+        if (threadIdx.x == 0) wait_stats(wait);
     } else {
         // workgroup 0: every workgroup's moments (its own from above), in turns of one per lane
         if (threadIdx.x != 0) { v[0] = v[1] = v[2] = 0.0; }
         for (int64_t i = threadIdx.x; i < G; i += blockDim.x) {
             if (i == 0) continue;
             double m[3];
-            get_tagged<3>(rec + 6 * i, tag, m, 1);
+            get_tagged<3>(rec + 6 * i, tag, m, 1, kMaxPolls);
 #pragma unroll
             for (int q = 0; q < 3; ++q) v[q] += m[q];
         }
@@ -667,17 +731,34 @@ __global__ void __launch_bounds__(kMaskedWaves * kWave) masked_gae_fused_kernel(
                 stats[0] = m;
                 stats[1] = r;
                 st_relaxed(gen_word, uint64_t(((tag - 1u) / 2u + 1u) & 0x7fffffffu));
+                s_have = true;
                 s_mean = float(m);
                 s_rstd = float(r);
             }
         }
     }
     __syncthreads();
+    const bool full = can_full && c.valid == MaskedChunk<DT, K, TR, HM>::kAll;
+    if (!s_have) {  // waited long enough: the rest is workgroup 0's, unless it has closed
+        c.store(a.out0, full, c.adv);
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0 && !leave(ws, g, tag)) wait_stats(kMaxPolls);
+        __syncthreads();
+        if (!s_have) return;
+    }
     const float mean = s_mean, rstd = s_rstd;
+    uint64_t closed = 0;
+    if (g == 0 && G > 1 && threadIdx.x == 0)
+        closed = exchange(reinterpret_cast<uint64_t*>(ws + kMaskedCloseOff), uint64_t(tag) << 32);
     float y[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) y[k] = (c.adv[k] - mean) * rstd;
-    c.store(a.out0, can_full && c.valid == MaskedChunk<DT, K, TR, HM>::kAll, y);
+    c.store(a.out0, full, y);
+    if (g != 0 || G == 1) return;
+    if (threadIdx.x == 0) s_leavers = uint32_t(closed);
+    __syncthreads();
+    if (s_leavers) whiten_left(ws, tag, G, a.out0, rows_per_wg, a.N, a.T, mean, rstd);
 }
 
 }  // namespace rlcs

@@ -12,9 +12,10 @@ using namespace rlcs::host;
 namespace {
 
 // Bytes of the whitening workspace of an [N, T] call (at most one workgroup per row): the
-// 64-byte header (statistics, arrival word, statistics record), the one-pass form's moments
-// records (kFusedMaxGroups of 48 bytes), then the two-pass form's partials: one 32-byte
-// partial per workgroup (room for N), then one per block of kDirectPartials partials.
+// 64-byte header (statistics, generation, the call's word), the one-pass form's moments and
+// statistics records, then the two-pass form's partials: one 32-byte
+// partial per workgroup (room for N; the one-pass form's hand words lie in them), then one per block
+// of kDirectPartials partials.
 constexpr size_t masked_rows(int64_t N) { return size_t(N > 0 ? N : 1); }
 constexpr size_t masked_ws_need(int64_t N) {
     return kMaskedTwoPassOff +
@@ -32,15 +33,21 @@ void launch_masked(const MaskedArgs& ma, int waves, int64_t groups, int64_t rows
                        dim3(unsigned(waves * kWave)), masked_lds<DT>(waves), s, ma, rows_per_wg, wave_local);
 }
 
-// The one-pass whitened call when its grid is resident at once; false when it is not (the caller
-// then runs the two-pass form).
+// The one-pass whitened call when its grid is resident at once on an idle GPU; false when it is not
+// (the caller then runs the two-pass form, which is faster than workgroups that leave). Each SIMD
+// takes a quarter of a workgroup's waves, rounded up, so ten waves take the room of twelve: counted
+// as ten, 768 workgroups would seem to fit (float32 rows of 2049 to 2560 steps) where 512 do.
 template <typename DT, bool VEC, bool TR, bool HM>
 bool launch_fused(const MaskedArgs& ma, int waves, int64_t groups, int64_t rows_per_wg, int wave_local,
                   float eps, void* ws, hipStream_t s) {
     const auto kernel = masked_gae_fused_kernel<DT, Width<DT>::K, VEC, TR, HM>;
-    if (groups > resident_groups(kernel, waves * kWave, masked_lds<DT>(waves))) return false;
+    constexpr int kSimds = 4;
+    if (g_whitening_wait < 0 &&
+        groups > resident_groups(kernel, (waves + kSimds - 1) / kSimds * kSimds * kWave, masked_lds<DT>(waves)))
+        return false;
+    const uint32_t wait = g_whitening_wait < 0 ? kWaitPolls : uint32_t(g_whitening_wait);
     hipLaunchKernelGGL(kernel, dim3(unsigned(groups)), dim3(unsigned(waves * kWave)), masked_lds<DT>(waves), s,
-                       ma, rows_per_wg, wave_local, eps, static_cast<char*>(ws));
+                       ma, rows_per_wg, wave_local, eps, static_cast<char*>(ws), wait);
     return true;
 }
 

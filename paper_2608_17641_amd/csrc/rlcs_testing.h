@@ -1,4 +1,4 @@
-// Test-only entry point of librlcs.so, not part of the public interface in rlcs.h.
+// Test-only entry points of librlcs.so, not part of the public interface in rlcs.h.
 #pragma once
 
 #include "rlcs.h"
@@ -17,6 +17,12 @@ extern "C" {
  * in arrival order (needs the workspace; at most 1024 groups and more than 64 steps, else as
  * with 0; row-major calls as with 0). Returns RLCS_ERR_INVALID_ARG for other values. */
 rlcs_status rlcs_testing_set_variant(int variant);
+
+/* One-pass whitened masked GAE of the calling thread's later calls: polls >= 0 launches it whether
+ * or not its grid is resident at once, and its workgroups leave after that many polls for the
+ * statistics (0: after the first look); -1 = as without this call. Returns RLCS_ERR_INVALID_ARG for
+ * other values. */
+rlcs_status rlcs_testing_set_whitening_wait(int polls);
 
 #ifdef __cplusplus
 }
