@@ -60,6 +60,24 @@ inline int balanced_waves(int64_t steps, int64_t K) {
     return int((steps + span - 1) / span);
 }
 
+// Waves of a workgroup for rows of T steps, more than four waves hold. One row to a workgroup in as few
+// chunks as sixteen waves allow, of as many waves as these chunks need; but sixteen waves, with
+// two or three rows to a workgroup, for
+//   bfloat16 rows of five to eight waves that do not fill them (one row against several: 1000 x 2500
+//   with truncation 20.3 and 16.5 us, 2048 x 4090 44.9 and 35.4; 2048 x 4096, which fills eight
+//   waves, 30.5 and 35.2);
+//   float32 rows of six to eight waves the last of which is more than half idle (2048 x 1300 17.7 and
+//   15.7 us, 512 x 1800 6.7 and 6.0; 2048 x 1500 19.1 and 20.7).
+template <typename DT>
+int row_waves(int64_t T, int64_t slack) {
+    constexpr int64_t span = int64_t(kWave) * Width<DT>::K;
+    const int W = balanced_waves(T + slack, Width<DT>::K);
+    const int64_t idle = W * span - T - slack;
+    if (2 * T + slack > kMaskedWaves * span) return W;
+    if (sizeof(DT) == 2) return idle ? kMaskedWaves : W;
+    return W > 5 && idle > span / 2 ? kMaskedWaves : W;
+}
+
 template <typename DT>
 rlcs_status run_masked(MaskedArgs& ma, bool normalize, float eps, void* ws, hipStream_t s) {
     constexpr int K = Width<DT>::K;
@@ -71,9 +89,7 @@ rlcs_status run_masked(MaskedArgs& ma, bool normalize, float eps, void* ws, hipS
     // normalize workgroup adds up (12.4 -> 13.6 us), so those calls keep four waves.
     const bool one_wave = !normalize && T % K == 0 && (int64_t(kWave) * K) % T == 0 && T >= 32 * K;
     const int64_t slack = (T % K == 0) ? 0 : K - 1;
-    // Longer rows: one to a workgroup, in as few chunks as sixteen waves allow, of as many waves as
-    // these chunks need.
-    const int waves = (T <= E_small) ? (one_wave ? 1 : kSmallWaves) : balanced_waves(T + slack, K);
+    const int waves = (T <= E_small) ? (one_wave ? 1 : kSmallWaves) : row_waves<DT>(T, slack);
     const int64_t E = int64_t(waves) * kWave * K;
     const int64_t rows_per_wg = (T <= E - slack) ? (E - slack) / T : 1;
     const int64_t groups = (N + rows_per_wg - 1) / rows_per_wg;

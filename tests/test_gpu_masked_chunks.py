@@ -44,3 +44,21 @@ def test_many_groups_whitened(N, T):
     mask = (np.random.default_rng(N).random((N, T)) < 0.7).astype(np.uint8)
     out, ref = run(ro, mask, normalize=True)
     assert_parity(out, ref, TOL["f32"], label=f"{N}x{T}")
+
+
+@pytest.mark.parametrize("dtype,N,T", [("bf16", 7, 2049), ("bf16", 8, 2100), ("bf16", 9, 4090), ("bf16", 5, 4092),
+                                       ("bf16", 4, 4093), ("bf16", 3, 4096), ("f32", 7, 1300), ("f32", 8, 1800),
+                                       ("f32", 5, 2046), ("f32", 4, 2047), ("f32", 4, 2048)])
+def test_several_long_rows_to_a_workgroup(dtype, N, T):
+    """Rows of five to nine waves that sixteen waves hold two or three of, and the lengths beside
+    them; whole workgroups and a last one of fewer rows."""
+    ro = workloads.make_rollout(N, T, seed=N + T, dtype=dtype, p_term=0.002, p_trunc=0.002)
+    mask = (np.random.default_rng(T).random((N, T)) < 0.5).astype(np.uint8)
+    mask[1] = 0
+    mask[2, T // 8:T - T // 8] = 0
+    for trunc in (True, False):
+        out, ref = run(ro, mask, trunc=trunc)
+        assert_parity(out, ref, TOL[dtype], label=f"{N}x{T} {dtype} trunc={trunc}")
+    with variant(1):
+        out, ref = run(ro, mask, normalize=True)
+    assert_parity(out, ref, TOL[dtype], label=f"{N}x{T} {dtype} two passes")
