@@ -15,6 +15,7 @@ GPU. ``ws`` is an optional zero-initialised uint8 workspace (see ``make_workspac
 from __future__ import annotations
 
 import contextlib
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -36,9 +37,24 @@ __all__ = [
 _fast = None  # the native functions, once loaded
 
 
+class _Interpreted:
+    """Stands for the native functions where there are none: leaves every call to Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
+
+
 def _load_fast():
+    """The native functions. Without them every call runs in Python: with a warning, once, where
+    only the binding is missing; where librlcs.so is, a call with good arguments raises in load()."""
     global _fast
-    _fast = _native.binding()
+    try:
+        _fast = _native.binding()
+    except _native.BindingUnavailable as e:
+        warnings.warn(f"{e}; calls take the slower Python path", RuntimeWarning, stacklevel=3)
+        _fast = _Interpreted()
+    except RuntimeError:
+        return _Interpreted()
     return _fast
 
 

@@ -8,7 +8,7 @@ import ctypes
 import importlib.util
 import os
 
-from .build import BINDING_LIB, LIB
+from .build import LIB, binding_lib
 
 RLCS_OK = 0
 RLCS_ERR_INVALID_ARG = 1
@@ -107,19 +107,26 @@ class RlcsError(RuntimeError):
 _binding = None
 
 
+class BindingUnavailable(RuntimeError):
+    """The native binding is not built for the running Python and PyTorch, or does not load."""
+
+
 def binding():
-    """The native side of the binding (csrc/binding.cpp), bound to librlcs.so. Raises if it has
-    not been built."""
+    """The native side of the binding (csrc/binding.cpp), bound to librlcs.so. Raises RuntimeError
+    if librlcs.so has not been built, BindingUnavailable if only the binding cannot be had."""
     global _binding
     if _binding is None:
         lib = load()
-        if not os.path.exists(BINDING_LIB):
-            raise RuntimeError(
-                f"{BINDING_LIB} is missing: build it first (python -m paper_2608_17641_amd.build "
-                "or __graft_entry__.build())")
-        spec = importlib.util.spec_from_file_location(__package__ + "._binding", BINDING_LIB)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
-        module.bind(lib._handle, RlcsError)
+        path = binding_lib()
+        again = "build it (python -m paper_2608_17641_amd.build or __graft_entry__.build())"
+        if not os.path.exists(path):
+            raise BindingUnavailable(f"{path} is missing: {again}")
+        try:
+            spec = importlib.util.spec_from_file_location(__package__ + "._binding", path)
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            module.bind(lib._handle, RlcsError)
+        except (ImportError, OSError) as e:
+            raise BindingUnavailable(f"{path} does not load ({e}): {again}") from e
         _binding = module
     return _binding

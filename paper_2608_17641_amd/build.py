@@ -7,8 +7,9 @@ produces ``paper_2608_17641_amd/librlcs.so`` from the translation units ``csrc/r
 the public header ``include/rlcs.h``, and ``paper_2608_17641_amd/libprobe.so`` from
 ``csrc/probe_stream.hip``: reference kernels that bench.py times beside the library (a streaming
 copy with GAE's byte split, an empty launch), not part of the library; and
-``paper_2608_17641_amd/_binding.so`` from ``csrc/binding.cpp``, the native side of the Python
-binding (host code only, g++ against PyTorch's headers).
+``paper_2608_17641_amd/_binding.<python>-torch<version>.so`` from ``csrc/binding.cpp``, the native
+side of the Python binding (host code only, g++ against PyTorch's headers, so built once for each
+Python and PyTorch it is to run with).
 """
 from __future__ import annotations
 
@@ -27,7 +28,6 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librlcs.so")
 PROBE_LIB = os.path.join(PKG, "libprobe.so")
 PROBE_SOURCE = os.path.join(CSRC, "probe_stream.hip")
-BINDING_LIB = os.path.join(PKG, "_binding.so")
 BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 SOURCES = sorted(glob.glob(os.path.join(CSRC, "rlcs_*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "rlcs_*.h"))) + [os.path.join(INCLUDE, "rlcs.h")]
@@ -65,7 +65,13 @@ def link_command(objs, out: str = LIB):
     return [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out, *objs]
 
 
-def binding_command(out: str = BINDING_LIB):
+def binding_lib() -> str:
+    """The native binding of the running Python and PyTorch, built or not."""
+    import torch
+    return os.path.join(PKG, f"_binding.{sys.implementation.cache_tag}-torch{torch.__version__}.so")
+
+
+def binding_command(out: str):
     import sysconfig
 
     import torch
@@ -80,13 +86,6 @@ def binding_command(out: str = BINDING_LIB):
             "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
-def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
-
-
 _NOISE = ("is not a recognized feature for this target", "(ignoring feature)")
 
 
@@ -97,34 +96,37 @@ def _run(cmd):
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile librlcs.so, libprobe.so and _binding.so: always when force, else only if one of
-    them does not exist yet."""
-    if not force and all(os.path.exists(p) for p in (LIB, PROBE_LIB, BINDING_LIB)):
-        return LIB
+    """Compile librlcs.so, libprobe.so and the native binding: all of them when force, else those
+    that do not exist yet (a binding for another Python or PyTorch does not count)."""
+    binding = binding_lib()
+    jobs = {}  # output -> (objects to link, sources to compile into them)
     with tempfile.TemporaryDirectory(prefix="rlcs_build_") as tmpdir:
-        objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in SOURCES]
-        probe_obj = os.path.join(tmpdir, "probe_stream.o")
-        jobs = min(len(SOURCES) + 1, max(1, min(8, os.cpu_count() or 1)))
-        binding_tmp = BINDING_LIB + f".tmp{os.getpid()}"
-        with ThreadPoolExecutor(max_workers=jobs + 1) as pool:
-            binding = pool.submit(_run, binding_command(binding_tmp))
-            results = list(pool.map(lambda so: (so[0], _run(compile_command(*so))),
-                                    list(zip(SOURCES, objs)) + [(PROBE_SOURCE, probe_obj)]))
-            results.append((BINDING_SOURCE, binding.result()))
+        for out, sources in ((LIB, SOURCES), (PROBE_LIB, [PROBE_SOURCE])):
+            if force or not os.path.exists(out):
+                jobs[out] = [(src, os.path.join(tmpdir, os.path.basename(src) + ".o")) for src in sources]
+        want_binding = force or not os.path.exists(binding)
+        binding_tmp = binding + f".tmp{os.getpid()}"
+        with ThreadPoolExecutor(max_workers=max(1, min(8, os.cpu_count() or 1)) + 1) as pool:
+            pending = pool.submit(_run, binding_command(binding_tmp)) if want_binding else None
+            compiles = [so for pairs in jobs.values() for so in pairs]
+            results = list(pool.map(lambda so: (so[0], _run(compile_command(*so))), compiles))
+            if pending:
+                results.append((BINDING_SOURCE, pending.result()))
         for src, (rc, err) in results:
             if rc != 0:
                 raise RuntimeError(f"compiling {src} failed ({rc}):\n{err}")
             if verbose and err.strip():
                 print(err, file=sys.stderr)
-        for objects, out in ((objs, LIB), ([probe_obj], PROBE_LIB)):
+        for out, pairs in jobs.items():
             tmp = out + f".tmp{os.getpid()}"
-            rc, err = _run(link_command(objects, tmp))
+            rc, err = _run(link_command([obj for _, obj in pairs], tmp))
             if rc != 0:
                 if os.path.exists(tmp):
                     os.remove(tmp)
                 raise RuntimeError(f"link of {os.path.basename(out)} failed ({rc}):\n{err}")
             os.replace(tmp, out)
-        os.replace(binding_tmp, BINDING_LIB)
+        if want_binding:
+            os.replace(binding_tmp, binding)
     return LIB
 
 

@@ -1,0 +1,71 @@
+"""The native binding is built for one Python and PyTorch: another's is not taken for it, and where
+it cannot be had the package's functions work as before, in Python."""
+import os
+import sys
+import warnings
+
+import pytest
+import torch
+
+import paper_2608_17641_amd as rl
+from paper_2608_17641_amd import _native, build
+
+
+def test_file_names_python_and_torch():
+    name = os.path.basename(build.binding_lib())
+    assert sys.implementation.cache_tag in name and torch.__version__ in name
+
+
+def test_another_torch_is_built_for(monkeypatch, tmp_path):
+    """build(force=False) with everything there but this PyTorch's binding compiles only that."""
+    for attr in ("LIB", "PROBE_LIB"):
+        path = tmp_path / attr
+        path.touch()
+        monkeypatch.setattr(build, attr, str(path))
+    (tmp_path / "_binding.cpython-39-torch1.0.so").touch()
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    commands = []
+
+    def run(cmd):
+        commands.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return 0, ""
+
+    monkeypatch.setattr(build, "_run", run)
+    build.build(force=False)
+    assert len(commands) == 1 and build.BINDING_SOURCE in commands[0]
+    assert os.path.exists(build.binding_lib())
+    build.build(force=False)
+    assert len(commands) == 1
+
+
+@pytest.mark.parametrize("broken", ["missing", "unloadable"])
+def test_without_binding(monkeypatch, tmp_path, broken):
+    """One warning; a bad argument is still reported as such."""
+    path = tmp_path / "_binding.so"
+    if broken == "unloadable":
+        path.write_bytes(b"not a library")
+    monkeypatch.setattr(_native, "binding_lib", lambda: str(path))
+    monkeypatch.setattr(_native, "_binding", None)
+    monkeypatch.setattr(rl, "_fast", None)
+    x = torch.zeros(2, 8)
+    with pytest.warns(RuntimeWarning, match="Python path"):
+        with pytest.raises(ValueError, match="must be on a GPU"):
+            rl.rlcs_gae(x, x, gamma=0.9, lam=0.9)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        with pytest.raises(ValueError, match="must be on a GPU"):
+            rl.rlcs_elig_trace(x, gamma=0.9, lam=0.9)
+
+
+def test_without_library(monkeypatch, tmp_path):
+    """Arguments are checked before the library is asked for."""
+    monkeypatch.setattr(_native, "LIB", str(tmp_path / "librlcs.so"))
+    monkeypatch.setattr(_native, "_lib", None)
+    monkeypatch.setattr(_native, "_binding", None)
+    monkeypatch.setattr(rl, "_fast", None)
+    x = torch.zeros(2, 8)
+    with pytest.raises(ValueError, match="must be on a GPU"):
+        rl.rlcs_gae(x, x, gamma=0.9, lam=0.9)
+    with pytest.raises(RuntimeError, match="is missing"):
+        rl.make_workspace(2, 8, "cpu")
