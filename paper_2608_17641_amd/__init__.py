@@ -600,10 +600,11 @@ def rlcs_gae_masked(r, v, mask=None, term=None, trunc=None, bv=None, boot=None, 
     the advantages whitened over the steps that take part. A zero-filled workspace for
     whitening is allocated when none is given (a workspace passed in must have been zero-filled
     before its first use)."""
-    done = (_fast or _load_fast()).gae_masked(r, v, mask, term, trunc, bv, boot, adv, ret, gamma,
-        lam, normalize, eps, want_ret, ws)
-    if done is not NotImplemented:
-        return done
+    if ws is not None or not normalize:  # (otherwise the workspace is made here)
+        done = (_fast or _load_fast()).gae_masked(r, v, mask, term, trunc, bv, boot, adv, ret, gamma,
+            lam, normalize, eps, want_ret, ws)
+        if done is not NotImplemented:
+            return done
     N, T, dt, dev = _prep(r)
     _check_data("v", v, N, T, dt, dev); _check_data("bv", bv, N, T, dt, dev)
     _check_data("boot", boot, N, T, dt, dev, shape=(N,))

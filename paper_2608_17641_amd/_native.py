@@ -125,7 +125,8 @@ def binding():
             spec = importlib.util.spec_from_file_location(__package__ + "._binding", path)
             module = importlib.util.module_from_spec(spec)
             spec.loader.exec_module(module)
-            module.bind(lib._handle, RlcsError)
+            from torch.utils._device import DeviceContext
+            module.bind(lib._handle, RlcsError, DeviceContext)
         except (ImportError, OSError) as e:
             raise BindingUnavailable(f"{path} does not load ({e}): {again}") from e
         _binding = module

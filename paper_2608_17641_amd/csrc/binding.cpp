@@ -6,8 +6,8 @@
 // checks, allocate the missing outputs and call the C interface on the current stream.
 //
 // They only take calls that are plain in every respect (tensors of exactly torch's own type on
-// the current GPU, right shapes and types, no active dispatch or function mode) and return
-// NotImplemented for any other, having done nothing: the Python function then runs its own checks
+// the current GPU, right shapes and types, no active dispatch mode, no function mode but torch's
+// default device) and return NotImplemented for any other, having done nothing: the Python function then runs its own checks
 // and reports what is wrong, or handles the call. So every error a caller sees about its arguments
 // comes from one place. Errors of the C interface are raised here as they are there.
 #include <Python.h>
@@ -18,13 +18,15 @@
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
+#include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "rlcs.h"
 
 namespace {
 
-PyObject* g_error = nullptr;  // RlcsError(fn, code)
+PyObject* g_error = nullptr;   // RlcsError(fn, code)
+PyObject* g_device = nullptr;  // torch.utils._device.DeviceContext
 
 // The library's functions, looked up in the handle the package loaded.
 struct Library {
@@ -62,6 +64,16 @@ const c10::DispatchKeySet kSpecial({c10::DispatchKey::Python, c10::DispatchKey::
                                     c10::DispatchKey::Functionalize, c10::DispatchKey::Conjugate,
                                     c10::DispatchKey::Negative, c10::DispatchKey::ZeroTensor});
 
+// Whether the function modes in force leave the call as it is: none, or torch's default device
+// (torch.set_default_device, `with torch.device(...)`), which only gives a device to factory
+// functions called without one. Every allocation here names its device.
+bool modes_pass() {
+    using TLS = at::impl::PythonTorchFunctionTLS;
+    for (int64_t i = 0, n = TLS::stack_len(); i < n; ++i)
+        if (reinterpret_cast<PyObject*>(Py_TYPE(TLS::get_stack_at(i)->ptr(getPyInterpreter()))) != g_device) return false;
+    return true;
+}
+
 // One call: its shape, and whether every argument seen so far is a plain one.
 struct Call {
     bool ok = true;
@@ -73,7 +85,7 @@ struct Call {
 
     explicit Call(bool s) : strided(s) {
         ok = g_bound && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
-             at::impl::PythonTorchFunctionTLS::stack_len() == 0;
+             modes_pass();
     }
 
     bool bf16() const { return dtype == at::kBFloat16; }
@@ -469,11 +481,12 @@ PyObject* gae_masked(Argv x, Py_ssize_t nargs) {
     });
 }
 
-// bind(handle, error): the dlopen handle of librlcs.so and the exception class of its status codes
+// bind(handle, error, device): the dlopen handle of librlcs.so, the exception class of its status
+// codes and the class of torch's default-device mode
 PyObject* bind(PyObject*, PyObject* args) {
     unsigned long long handle = 0;
-    PyObject* error = nullptr;
-    if (!PyArg_ParseTuple(args, "KO", &handle, &error)) return nullptr;
+    PyObject *error = nullptr, *device = nullptr;
+    if (!PyArg_ParseTuple(args, "KOO", &handle, &error, &device)) return nullptr;
     void* h = reinterpret_cast<void*>(handle);
     bool all = true;
     auto get = [&](auto& fn, const char* name) {
@@ -505,6 +518,8 @@ PyObject* bind(PyObject*, PyObject* args) {
     }
     Py_INCREF(error);
     Py_XSETREF(g_error, error);
+    Py_INCREF(device);
+    Py_XSETREF(g_device, device);
     g_bound = true;
     Py_RETURN_NONE;
 }

@@ -211,3 +211,30 @@ def test_left_to_python(sides):
             sides(side, lambda: torch.func.vmap(lambda x: rl.rlcs_discounted(x, gamma=0.9))(r[None]))
     empty, taken = sides("native", lambda: rl.rlcs_discounted(r[:0], gamma=0.9))
     assert taken == [True] and empty.shape == (0, 16)
+
+
+def test_default_device(sides):
+    """torch's default device is a function mode too; it changes nothing for a call whose
+    allocations all name their device, and another mode beside it still leaves the call to Python."""
+    from torch.overrides import TorchFunctionMode
+
+    class Function(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    r = torch.randn(8, 16, device="cuda")
+    ref = rl.rlcs_discounted(r, gamma=0.9)
+    call = lambda: rl.rlcs_discounted(r, gamma=0.9)
+    for device in ("cuda", "cpu"):
+        with torch.device(device):
+            out, taken = sides("native", call)
+            assert taken == [True] and out.is_cuda and torch.equal(out, ref)
+            with Function():
+                out, taken = sides("native", call)
+            assert taken == [False] and torch.equal(out, ref)
+    torch.set_default_device("cuda")
+    try:
+        out, taken = sides("native", call)
+    finally:
+        torch.set_default_device(None)
+    assert taken == [True] and torch.equal(out, ref)
