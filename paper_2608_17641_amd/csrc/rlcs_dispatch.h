@@ -97,7 +97,6 @@ struct Plan {
     int waves;            // waves per workgroup
     int64_t tiles_per_row;  // tiles kernel: tiles of each row (grid = N * tiles_per_row)
     int64_t rows_per_wg;  // rows kernel: rows per workgroup
-    int wave_local;       // rows kernel: no carry crosses waves
     bool pad;             // rows kernel, vector path: lanes outside the range or in row gaps skip
     int wave_rows_log2T;  // >= 0: wave_rows_kernel (rows tile a wave exactly; T = 2^log2T)
     int flat_R;           // > 0: flat_rows_kernel with this many whole rows per workgroup
@@ -144,7 +143,7 @@ void launch_w(const Args& a, const Plan& p, hipStream_t stream) {
     }
     const int64_t groups = (a.N + p.rows_per_wg - 1) / p.rows_per_wg;
     hipLaunchKernelGGL((rows_kernel<Op, DT, K, W, VEC, TR, PAD>), dim3(unsigned(groups)), block,
-                       0, stream, a, p.rows_per_wg, p.wave_local);
+                       0, stream, a, p.rows_per_wg);
 }
 
 template <class Op, typename DT, bool VEC, bool TR>
@@ -301,8 +300,6 @@ rlcs_status dispatch_dt(Args& a, bool has_trunc, void* ws, size_t ws_bytes, hipS
         const int64_t slack = (T % K == 0) ? 0 : K - 1;
         p.rows_per_wg = (T <= E - slack) ? (E - slack) / T : 1;
         if ((N + p.rows_per_wg - 1) / p.rows_per_wg > INT32_MAX) return RLCS_ERR_INVALID_ARG;
-        // Rows never straddle waves when T divides a wave's span (and is a multiple of K).
-        p.wave_local = (T % K == 0 && (int64_t(kWave) * K) % T == 0) ? 1 : 0;
         // When a workgroup's rows do not fill its chunks exactly, every chunk still takes the
         // vector path lane by lane: only the lanes at the ragged ends of the workgroup's range
         // go element-wise.
@@ -328,9 +325,10 @@ rlcs_status dispatch(Args& a, rlcs_dtype dtype, bool has_trunc, void* ws, size_t
     return dispatch_dt<Op, float>(a, has_trunc, ws, ws_bytes, s);
 }
 
-// Rows with a row stride (period) above T: the rows kernel over the positions n * period + t
-// (the steps t >= T of each period are skipped), whole rows per workgroup; vector loads and
-// stores where a lane's steps allow when the arrays are aligned, else element-wise.
+// Rows with a row stride (period) above T, whole rows per workgroup: the ragged rows kernel where one
+// workgroup holds a row, except as below; otherwise the rows kernel over the positions
+// n * period + t (the steps t >= T of each period are skipped), vector loads and stores where a lane's
+// steps allow when the arrays are aligned, else element-wise.
 template <class Op>
 rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, bool has_trunc,
                                   rlcs_stream_t stream) {
@@ -381,7 +379,6 @@ rlcs_status dispatch_strided_rows(Args& a, int64_t period, rlcs_dtype dtype, boo
         // as many rows as fit in one chunk: the last one's gap is not part of the range
         p.rows_per_wg = (a.T <= E - slack) ? (E - slack - a.T) / period + 1 : 1;
         if ((a.N + p.rows_per_wg - 1) / p.rows_per_wg > INT32_MAX) return RLCS_ERR_INVALID_ARG;
-        p.wave_local = 0;
         p.wave_rows_log2T = -1;
         p.flat_R = 0;
         p.flat_W = kSmallWaves;

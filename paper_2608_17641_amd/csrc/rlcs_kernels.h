@@ -1,6 +1,8 @@
-// The two kernel shapes that run every estimator.
-//
-// Both treat the [N, T] buffer as one flat array of N*T steps and run a segmented scan over it:
+// The kernels of row-major calls: wave_rows_kernel (rows that tile a wave), flat_rows_kernel (rows of
+// whole vectors), ragged_rows_kernel (rows of any length and alignment, and rows a stride apart),
+// each for rows of up to one workgroup, then rows_kernel (whole rows, chunk by chunk) and
+// tiles_kernel (rows split over workgroups) for what is left. The last two, described here,
+// treat the [N, T] buffer as one flat array of N*T steps and run a segmented scan over it:
 // each lane owns K consecutive steps (one 16-byte vector per input), a wave owns 64*K steps and
 // a workgroup of W waves a chunk of E = W*64*K steps. Per chunk:
 //   1. load every input once (coalesced vector loads), with the carry-source neighbour of the
@@ -356,14 +358,13 @@ struct Chunk {
         if (needs_nbr(lane)) Op::template nbr_load_raw<DT>(a, kBack ? p0 + K : p0 - 1, nraw);
     }
 
-    // Steps 1-4. Writes the wave's map to s_a/s_b[wave] unless `wave_local`; the caller
-    // synchronises.
+    // Steps 1-4. Writes the wave's map to s_a/s_b[wave]; the caller synchronises.
     template <bool FULL, class BaseFn>
     __device__ void local_scan(const Args& a, int64_t chunk_lo, int64_t lo, int64_t hi,
-                               float* s_a, float* s_b, int lane, int wave, bool wave_local,
-                               BaseFn&& base_of, float* s_d = nullptr) {
+                               float* s_a, float* s_b, int lane, int wave, BaseFn&& base_of,
+                               float* s_d = nullptr) {
         if constexpr (kCanDefer) {
-            defer_chunk_ = FULL && s_d != nullptr && !wave_local;
+            defer_chunk_ = FULL && s_d != nullptr;
             defer_ = defer_chunk_ && wave > 0;
         }
         sidx = (wave * kWave + lane_group<kBack>(lane)) * K;
@@ -404,7 +405,7 @@ struct Chunk {
             for (int k = 1; k < K; ++k) agg = compose(Pair{al[k], be[k]}, agg);
         }
         incl = wave_scan_inclusive(agg, lane);
-        if (!wave_local && lane == kWave - 1) {
+        if (lane == kWave - 1) {
             s_a[wave] = incl.a;
             s_b[wave] = incl.b;
             if constexpr (kCanDefer) {
@@ -491,29 +492,22 @@ struct Chunk {
     }
 };
 
-// One chunk: local scan, the wave composition (unless rows are wave-local) and, through
-// `carry_of`, the value entering the chunk; then the carry application and stores.
+// One chunk: local scan, the wave composition and, through `carry_of`, the value entering the
+// chunk; then the carry application and stores.
 template <bool FULL, class C, class BaseFn, class CarryFn>
 __device__ __forceinline__ float run_chunk(C& c, const Args& a, int64_t chunk_lo, int64_t lo,
                                            int64_t hi, float* s_a, float* s_b, float* s_d,
-                                           int lane, int wave, bool wave_local, BaseFn&& base_of,
-                                           CarryFn&& carry_of) {
-    c.template local_scan<FULL>(a, chunk_lo, lo, hi, s_a, s_b, lane, wave, wave_local, base_of, s_d);
-    if (wave_local) {
-        c.wave_in = identity_pair();
-    } else {
-        __syncthreads();
-        c.wave_prefix(s_a, s_b, wave, s_d);
-    }
+                                           int lane, int wave, BaseFn&& base_of, CarryFn&& carry_of) {
+    c.template local_scan<FULL>(a, chunk_lo, lo, hi, s_a, s_b, lane, wave, base_of, s_d);
+    __syncthreads();
+    c.wave_prefix(s_a, s_b, wave, s_d);
     return c.template finish<FULL>(a, carry_of());
 }
 
 // Rows kernel: workgroup g owns rows [g*R, g*R + R) and walks them in chunks of E steps
 // aligned to multiples of K, starting from the carry source (the end for backward scans).
-// `wave_local`: every wave's span starts and ends on row edges (T divides 64*K and the chunk
-// is row aligned), so no carry crosses waves and step 5 is skipped.
 template <class Op, typename DT, int K, int W, bool VEC, bool TR, bool PAD = false>
-__global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_per_wg, int wave_local) {
+__global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_per_wg) {
     using C = Chunk<Op, DT, K, W, VEC, TR, PAD>;
     constexpr int64_t E = int64_t(W) * kWave * K;
     __shared__ float s_a[W], s_b[W];
@@ -537,8 +531,8 @@ __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_pe
             C c;
             c.oslot = s_out[C::kLineStores ? wave : 0];
             const float first = (can_full && (PAD || (chunk_lo >= lo && chunk_hi <= hi)))
-                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of)
-                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of);
+                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, base_of, carry_of)
+                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, base_of, carry_of);
             if (chunk_lo <= lo) break;
             // the next chunk (earlier in time) continues from A at chunk_lo, held by lane 63 of
             // wave 0
@@ -553,8 +547,8 @@ __global__ void __launch_bounds__(W * kWave) rows_kernel(Args a, int64_t rows_pe
             C c;
             c.oslot = s_out[C::kLineStores ? wave : 0];
             const float last = (can_full && (PAD || (chunk_lo >= lo && chunk_lo + E <= hi)))
-                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of)
-                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, wave_local, base_of, carry_of);
+                ? run_chunk<true>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, base_of, carry_of)
+                : run_chunk<false>(c, a, chunk_lo, lo, hi, s_a, s_b, s_d, lane, wave, base_of, carry_of);
             if (chunk_lo + E >= hi) break;
             if (threadIdx.x == W * kWave - 1) s_carry = last;
             __syncthreads();
@@ -1138,8 +1132,8 @@ __global__ void __launch_bounds__(W * kWave) tiles_kernel(Args a, int64_t P) {
     // whole 16-byte vectors: a full tile whose rows start on a vector boundary
     const bool full = VEC && T % K == 0 && hi - lo == E;
     auto base_of = [&]() { return RowBase{lo, row, p * E}; };
-    if (full) c.template local_scan<true>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of);
-    else c.template local_scan<false>(a, lo, lo, hi, s_a, s_b, lane, wave, false, base_of);
+    if (full) c.template local_scan<true>(a, lo, lo, hi, s_a, s_b, lane, wave, base_of);
+    else c.template local_scan<false>(a, lo, lo, hi, s_a, s_b, lane, wave, base_of);
     __syncthreads();
     c.wave_prefix(s_a, s_b, wave);
 
