@@ -418,8 +418,9 @@ struct Chunk {
     // a deferring chunk, the cut of each wave's first step by the flag before it).
     __device__ void wave_prefix(const float* s_a, const float* s_b, int wave, const float* s_d = nullptr) {
         // (bfloat16 keeps the loop: GAE 435 x 21063 31.5 us against 32.3, where float32 gains,
-        // 300 x 8192 12.8 -> 12.0)
-        if constexpr (W > 8 && sizeof(DT) == 4) {
+        // 300 x 8192 12.8 -> 12.0; so do unaligned arrays, whose truncating kernels the row scan made
+        // slower, TD(lambda) 2000 x 4500 89 us against 64, 258 x 8047 28.0 against 22.8, and no other faster)
+        if constexpr (W > 8 && sizeof(DT) == 4 && VEC) {
             wave_in = waves_in<kBack>(s_a, s_b, W, wave, threadIdx.x & (kWave - 1));
             return;
         }
