@@ -13,7 +13,8 @@ namespace {
 // turn, float32, ordinary against non-temporal: 32 MB (4001 x 201 x 5) 13.8 against 15.3 us,
 // 59 MB (4096 x 256 x 7) 16.0 against 17.5; 100 MB (x 12) 26.1 against 23.6, 134 MB
 // (16384 x 256 x 4) 49.9 against 45.0, 151 MB (4096 x 256 x 18) 35.3 against 33.1, 537 MB (x 64)
-// 101 against 92.
+// 101 against 92; bfloat16 with K = 1, 134 MB (511 x 1024 x 64) 37.0 against 33.4, 96 MB (500 x 1000 x
+// 48) 32.9 against 30.4, 84 MB (2000 x 256 x 41) 31.5 against 30.6.
 constexpr int64_t kActCachedBytes = int64_t(80) << 20;
 
 // Calls of few actions (few bytes per step) scan K = 4 steps per lane, 256 per wave, from this
@@ -59,6 +60,9 @@ rlcs_status run_actions(const Args& a, hipStream_t s) {
     auto go = [&](auto lanes) -> rlcs_status {
         constexpr int L = decltype(lanes)::value;
         if constexpr (L <= kActFourLanes<DT>) {
+            if constexpr (sizeof(DT) == 2) {  // (so few steps of float32 are never above the limit)
+                if (!four && nt) return launch_actions<DT, L, 1, true>(a, s);
+            }
             if (!four) return launch_actions<DT, L, 1, false>(a, s);
             return nt ? launch_actions<DT, L, 4, true>(a, s) : launch_actions<DT, L, 4, false>(a, s);
         } else {

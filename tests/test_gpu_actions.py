@@ -69,3 +69,9 @@ def test_four_steps_per_lane(N, T, A, dtype):
 @pytest.mark.parametrize("dtype,N,T,A", [("f32", 4000, 257, 13), ("f32", 3001, 600, 7), ("bf16", 8001, 129, 33), ("f32", 1, 40000, 300)])
 def test_non_temporal_loads(dtype, N, T, A):
     _check(N, T, A, dtype, trunc=False, rows=slice(None, None, 211))
+
+
+@pytest.mark.parametrize("N,T,A", [(2001, 256, 41), (16001, 32, 64)])
+def test_non_temporal_loads_one_step_per_lane(N, T, A):
+    """bfloat16 calls of too few steps for four per lane whose Q and pi are past the cached size."""
+    _check(N, T, A, "bf16", shift=1, rows=slice(None, None, 211))
