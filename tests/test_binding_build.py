@@ -1,6 +1,7 @@
 """The native binding is built for one Python and PyTorch: another's is not taken for it, and where
 it cannot be had the package's functions work as before, in Python."""
 import os
+import struct
 import sys
 import warnings
 
@@ -69,3 +70,18 @@ def test_without_library(monkeypatch, tmp_path):
         rl.rlcs_gae(x, x, gamma=0.9, lam=0.9)
     with pytest.raises(RuntimeError, match="is missing"):
         rl.make_workspace(2, 8, "cpu")
+
+
+def test_no_thread_local_variables():
+    """A binding with a segment of thread-local variables slows every other library's (and with
+    them torch's own calls) down for as long as the process lives."""
+    path = build.binding_lib()
+    if not os.path.exists(path):
+        pytest.skip("the binding is not built")
+    with open(path, "rb") as f:
+        elf = f.read()
+    assert elf[:4] == b"\x7fELF" and elf[4] == 2  # 64-bit
+    phoff, = struct.unpack_from("<Q", elf, 32)
+    phentsize, phnum = struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, phoff + i * phentsize)[0] for i in range(phnum)]
+    assert 1 in kinds and 7 not in kinds  # PT_LOAD, PT_TLS
