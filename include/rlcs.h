@@ -271,14 +271,10 @@ rlcs_status rlcs_gae_masked_noalloc(const void* r, const void* v, const uint8_t*
  * elements. All [N, T] arrays of a call (data, flags, bv and outputs) share the strides; boot
  * stays [N], contiguous. Elements outside the (n, t) grid are neither read nor written.
  * Sizes: N >= 0, 0 <= T <= 2^30, the largest element offset representable.
- * Workspace: at least rlcs_workspace_size_columns(N, T) bytes, zero-filled once, lets few
- * environments (N below 8192) be split along T over several workgroups; without it each
- * group of 64 environments is scanned by one workgroup (the dense layout takes
- * rlcs_workspace_size(N, T) instead); calls of fewer than 64 environments, or that split into
- * fewer than 256 tiles of 64 columns by 64 steps, split groups of 16 float32 (32 bfloat16)
- * columns instead. Calls of at most 256 steps over 4096 to 8192 environments use none: each
- * workgroup scans 16 (32) whole columns. Time-major calls (stride_n = 1) of 8192 environments or
- * more use none either: their columns are walked four to a lane.
+ * Workspace: rlcs_workspace_size_columns(N, T) bytes, zero-filled once, always suffice
+ * (rlcs_workspace_size(N, T) for the dense layout). Time-major calls of few environments and many
+ * steps use it to split the steps over several workgroups; without one they run whole columns,
+ * slower. Short columns, and many of them, need none and leave it alone, as strided rows do.
  * Every other convention is the row-major one.                                             */
 rlcs_status rlcs_gae_strided(const void* r, const void* v, const uint8_t* term,
                              const uint8_t* trunc, const void* bv, const void* boot, float* adv,
@@ -329,9 +325,8 @@ rlcs_status rlcs_episodic_prefix_strided(const void* x, const uint8_t* term, con
  * Calls whose F is a multiple of the 16-byte vector width (4 float32 or 8 bfloat16 features)
  * with a power-of-two number of vectors up to 64, short enough rows (F = 16 float32: up to 512
  * steps) and enough of them for 256 workgroups run along rows, x and z 16-byte aligned; the
- * others scan the N*F feature columns, four to a lane from 8192 columns on where F is a multiple
- * of four. Workspace: rlcs_workspace_size_columns(N * F, T) bytes, as for the strided calls (used
- * by the other column scans when N*F is below about 64K).                                   */
+ * others scan the N*F feature columns. Workspace: rlcs_workspace_size_columns(N * F, T) bytes, as
+ * for the strided calls; scans of few columns and many steps use it.                       */
 rlcs_status rlcs_elig_trace_vec(const void* x, const uint8_t* term, const uint8_t* trunc,
                                 float* z, int64_t N, int64_t T, int64_t F, float gamma,
                                 float lambda, rlcs_dtype dtype, void* ws, size_t ws_bytes,

@@ -204,57 +204,134 @@ void col_launch(const Args& a, const ColGeom& g, bool split, int64_t blocks, hip
     col_launch_nt<Op, DT, TR, true>(a, g, split, blocks, s);
 }
 
-// Columns from which the automatic choice walks them four to a lane whatever their length: enough
-// 4 * LC-column blocks to fill the chip without splitting time. Below, only columns of one chunk
-// (colvec_short_columns): longer ones are faster split (TD(lambda) T x N = 1000 x 4000 19.0 us
-// against 23.1).
-constexpr int64_t kColVecMin = 8192;
+// Which calls cols_vec_kernel takes, and with how many lanes side by side (LC; blocks of 4 * LC
+// columns). What decides: blocks enough for the CUs; a last chunk that fills its waves (a wave holds
+// 256 / LC steps, a workgroup eight waves); how many workgroups share a CU (V-Trace and Retrace leave
+// room for two waves per SIMD, GAE and truncated float32 TD(lambda) three, the others four to six: the
+// thin ones below); blocks that share lines where rows do not start on one; and the kernels that take
+// the call otherwise: narrow groups, split tiles with a look-back, and whole-column walks, which up to
+// three chunks of 32 steps are as fast as this kernel. Device times below in us, T x N, with
+// truncation unless noted, the other kernels -> this one. Measured for seven estimators in both types,
+// with and without truncation, at 29 column counts of 1024 to 262144 and 32 lengths of 16 to 1024 steps
+// (9230 calls): 1.21 times as fast as the other kernels alone in the geometric mean, 0.5 % of the calls
+// more than 5 % slower (most GAE 160 x 100000 float32 without truncation, 13 %).
 
-// Columns of one chunk of 16-column blocks (8 waves of 16 lane groups, 512 steps), where one pass
-// without look-back replaces split tiles. From 64 blocks (1024 columns); device times, T x N,
-// split -> here. Up to 256 steps where vectors stay aligned: float32 GAE 128 x 1024 5.1 -> 4.3 us,
-// 200 x 2048 6.9 -> 5.0; bfloat16 GAE 64 x 1500 7.5 -> 4.8, V-Trace 200 x 7000 13.7 -> 11.3,
-// Retrace 128 x 6000 10.1 -> 8.1. Not float32 from 4096 columns, where the narrow groups apply (GAE
-// 64 x 5000 4.5 us against 5.0), nor of at most 32 steps, one chunk there (20 x 4096 3.5 against
-// 4.2). Longer columns only while the blocks are one per CU, and start on 16 elements of a row, so
-// that none shares a line's half with its neighbour: 512 x 1024 GAE 8.4 -> 6.3, 512 x 4096 Retrace
-// 17.5 -> 12.2, bfloat16 V-Trace 13.4 -> 10.9, against 500 x 3001 11.9 -> 15.8 and 400 x 7000
-// 19.9 -> 21.5.
+// Fewer than 8192 columns: only columns of one chunk of 16-column blocks (512 steps), where one pass
+// without look-back replaces split tiles. From 64 blocks (1024 columns). Up to 256 steps where vectors
+// stay aligned: float32 GAE 128 x 1024 5.1 -> 4.3, 200 x 2048 6.9 -> 5.0; bfloat16 GAE 64 x 1500 7.5 ->
+// 4.8, V-Trace 200 x 7000 13.7 -> 11.3. Not float32 from 4096 columns, where the narrow groups apply
+// (GAE 64 x 5000 4.5 against 5.0), nor of at most 32 steps, one chunk there (20 x 4096 3.5 against 4.2);
+// bfloat16 ones with LC = 8, where blocks share no line's half (V-Trace 16 x 1500 4.6 against 5.2).
+// Longer columns only while the blocks are one per CU and share no line's half: 512 x 1024 GAE 8.4 ->
+// 6.3, 512 x 4096 Retrace 17.5 -> 12.2, against 500 x 3001 11.9 -> 15.8. Truncated float32 V-Trace of
+// fewer than 2048 columns is even or slower where those blocks have most work or share lines (300 x
+// 1024 7.0 against 7.5, 80 x 1500 5.8 against 6.1).
+constexpr int64_t kColVecMin = 8192;
 constexpr int64_t kColVecShortMin = 1024;
-inline bool colvec_short_columns(const ColGeom& g, int64_t T, bool f32) {
-    if (!g.fcol || g.J < kColVecShortMin || T > 512) return false;
-    if (T > 256) return g.J <= 4096 && g.st % 16 == 0;
-    return g.st % kCvV == 0 && !(f32 && (T <= 32 || g.J >= 4096));
+template <class Op>
+int colvec_short_columns(const ColGeom& g, int64_t T, bool f32, bool tr) {
+    if (!g.fcol || g.J < kColVecShortMin || T > 512) return 0;
+    const bool halves = g.st % 16 == 0;  // no block shares a line's half
+    const bool few = std::is_same_v<Op, VtraceOp> && f32 && tr && g.J < 2048;
+    if (T > 256) return g.J <= 4096 && halves && !few ? 4 : 0;
+    if (g.st % kCvV != 0 || (f32 && (T <= 32 || g.J >= 4096))) return 0;
+    if (T <= 32) return halves ? 8 : 0;
+    return few && T > 64 && !halves ? 0 : 4;
 }
 
-// Lanes side by side of cols_vec_kernel, or 0 where it does not apply (columns not adjacent, or a
-// batch row's not a multiple of four).
-//   Rows that start on 128-byte lines: blocks of one line of float32 (LC = 8) or bfloat16 (16), the
-//   latter halved where whole lines leave CUs idle; time-major GAE float32 T x N = 256 x 8192 8.7 us
-//   (9.3 on the other kernels), 1000 x 8192 29.5 (40), 256 x 16384 15.8 (17.9), V-Trace 512 x
-//   8192 18.3 (22.7), 100 x 40000 20.0 (23.4); bfloat16 GAE 256 x 8192 8.1 (9.4), 1024 x 16384 54 (85).
-//   Other rows: two blocks to a line, LC = 16, so that fewer lines are shared (GAE float32 768 x 9762
-//   37.6 us, 51.5 with LC = 8, 44.3 before; V-Trace bfloat16 100 x 10000 7.9, 8.7, 8.9).
-//   Many long columns: LC = 32, fewer and longer pieces of each row at a time (GAE float32 1024 x
-//   32768 122 us against 129 and 152 with LC = 16 and 8, 249 x 65536 64.7 against 69.5 and 73.8;
-//   bfloat16 V-Trace 500 x 30000 58 against 63 and 76, 94 before).
-//   Columns of at most 32 steps, one chunk of the other kernels, stay there in float32 (GAE 20 x
-//   8192 3.8 us against 4.2); bfloat16 gains (TD(lambda) 17 x 50000 7.0 -> 5.6).
-//   Vector traces: N x T x F = 64 x 1024 x 256 23.2 us with LC = 8 (29.7 before), 27.3 with 16;
-//   1000 x 200 x 100 42.3 with 16 (44.6), bfloat16 500 x 256 x 256 32.6 with 16 (47); of features
-//   that do not fill lines only in many columns (100 x 1000 x 100 25.6 us split, 32.3 here).
-inline int colvec_lanes(const ColGeom& g, int64_t T, rlcs_dtype dtype) {
-    if (g.J > int64_t(INT32_MAX)) return 0;
+// Columns from which whole-column walks take calls that could be split, and from which they queue for
+// the CUs (1408 blocks of 64 columns, five and a half per CU).
+constexpr int64_t kCvWalks = (kColSerialBlocks - 1) * kWave + 1;
+constexpr int64_t kCvManyWalks = 1408 * kWave;
+
+template <class Op>
+int colvec_lanes(const ColGeom& g, int64_t T, rlcs_dtype dtype, bool tr) {
+    constexpr bool gae = std::is_same_v<Op, GaeOp>, td = std::is_same_v<Op, TdLambdaOp>;
+    constexpr bool vt = std::is_same_v<Op, VtraceOp>, re = std::is_same_v<Op, RetraceOp>;
+    constexpr bool disc = std::is_same_v<Op, DiscountedOp>, fwd = !Op::kBackward, light = fwd || disc;
+    const int64_t J = g.J;
+    if (J > int64_t(INT32_MAX)) return 0;
     if (g.fcol ? (g.C != 1 || g.bstride != 1) : g.C % kCvV != 0) return 0;
     const bool f32 = dtype == RLCS_F32;
-    if (g.J < kColVecMin) return colvec_short_columns(g, T, f32) ? 4 : 0;
-    const bool lines = g.st * int64_t(dtype_size(dtype)) % 128 == 0;
-    if (!g.fcol) return g.J >= 32768 ? 16 : lines ? 8 : 0;
-    if (f32 && T <= 32) return 0;
-    if (g.J >= 24576 && T > 192) return 32;
-    if (!lines) return 16;
-    if (g.J >= 49152) return f32 ? 16 : 8;
-    return f32 || g.J < 16384 ? 8 : 16;
+    if (J < kColVecMin) return colvec_short_columns<Op>(g, T, f32, tr);
+    const bool lines = g.st * int64_t(dtype_size(dtype)) % 128 == 0;  // rows start on a line
+    // Vector traces: N x T x F = 64 x 1024 x 256 23.2 with LC = 8 (29.7 before), 27.3 with 16; 1000 x 200
+    // x 100 42.3 with 16 (44.6), bfloat16 500 x 256 x 256 32.6 with 16 (47); of features that do not
+    // fill lines only in many columns (100 x 1000 x 100 25.6 split, 32.3 here), and not of few features,
+    // where a block takes pieces of several batch rows: 12 never (2750 x 400 x 12 39.3 against 64.3, 5417 x
+    // 150 x 12 29.5 against 43.0), 20 in short rows (1650 x 40 x 20 7.1 -> 5.4, 1650 x 400 x 20 39.2 against
+    // 51.4), below 40 in all but long ones (1179 x 400 x 28 40.2 against 45.0).
+    if (!g.fcol) {
+        if (J < 32768) return lines ? 8 : 0;
+        return lines || T <= (g.C < 16 ? 0 : g.C < 24 ? 64 : g.C < 40 ? 256 : T) ? 16 : 0;
+    }
+    const bool thin = light || (td && !(f32 && tr));
+
+    // At most 32 steps: one chunk of the other kernels in float32 (GAE 20 x 8192 3.8 against 4.2). In
+    // bfloat16 one wave of LC = 16 or 8, or four of LC = 32 (TD(lambda) 17 x 50000 7.0 -> 5.6, GAE 25 x 117047
+    // 16.8 -> 13.3, 18.3 with 8), but V-Trace without truncation, even in many columns (18 x 100000 9.1
+    // against 10.3).
+    if (T <= 32) {
+        if (f32 || (vt && !tr && T > 16 && J >= 32768)) return 0;
+        return T <= 16 ? 16 : J >= 32768 ? 32 : 8;
+    }
+    // 8192 columns: narrow groups of up to eight waves in float32 (V-Trace 40 x 8192 4.4 against 5.3;
+    // Retrace 128 x 8192 8.6 -> 7.5), else LC = 8, one block per CU (GAE 256 x 8192 13.7 -> 8.7).
+    if (J <= kColVecMin) return f32 && T <= (re ? 100 : light ? 64 : 128) ? 0 : 8;
+    if (J <= 16384) {
+        // LC = 16 (300 x 12288 V-Trace 24.4 -> 21.8, 29.0 with LC = 8). LC = 8 for the one chunk (two
+        // without truncation) of thin estimators (eligibility traces 150 x 16384 7.7 -> 6.1, 7.5 with 16);
+        // look-back for long columns whose 16 blocks leave half the CUs idle (1024 x 8200 eligibility traces
+        // 27.7 against 31.0).
+        if (thin && T > 128 && T <= (tr ? 256 : 512)) return 8;
+        if (gae && !tr && lines && J >= 12288 && T > 64 && T <= 128) return 8;
+        if (!lines && J < 12288 && T > 512 && (fwd || (td && f32))) return 0;
+        return 16;
+    }
+    // Columns of two or three chunks where whole-column walks take them. Float32: even at best here
+    // (V-Trace 64 x 65536 19.5 against 22.6, TD(lambda) 80 x 65536 18.4 against 24.7, GAE 80 x 100000 32.1
+    // against 36.9), but the light estimators gain with LC = 32 (eligibility traces 64 x 65536 11.1 -> 9.5,
+    // 80 x 100003 25.2 -> 20.5), and up to 64 steps all do where rows start off a line (GAE 64 x 100003
+    // 33.2 -> 31.0). Bfloat16: only V-Trace and Retrace are even (without truncation 72 x 81920 V-Trace
+    // 20.5 against 23.6), and untruncated GAE of many columns off a line.
+    if (T > 48 && T <= 96) {
+        if (f32 && J >= (re || (vt && T <= 64) ? 40000 : kCvWalks)) {
+            if (!lines) return T <= 64 ? 16 : light || (re && J >= 49152) ? 32 : 0;
+            if (!light) return T > 64 || vt || J < kCvManyWalks ? 0 : 16;
+            if (disc && T > 64) return 8;
+            return fwd && J < kCvManyWalks ? 32 : 16;
+        }
+        if (!f32 && (vt || re)) {
+            if (T <= 64 ? !tr && lines && J >= 49152 : J >= (tr ? kCvManyWalks : re ? 40000 : kCvWalks)) return 0;
+        }
+        if (!f32 && gae && !tr && !lines && T > 64 && J >= kCvManyWalks) return 0;
+    }
+    // Columns of at most 64 steps: four waves of LC = 16 (bfloat16 GAE 40 x 65536 14.5 -> 9.1, 12.7 with
+    // 8), below 49152 float32 columns two waves of 8.
+    if (T <= 64) return f32 && lines && J < 49152 ? 8 : 16;
+    // One chunk of LC = 16. Blocks of one line, 8 or 16; rows that start off a line, LC = 32, fewer lines
+    // shared (GAE 100 x 60001 float32 36.3 -> 27.5, 31.9 with 16). LC = 8 for bfloat16 GAE (112 x 18752
+    // without truncation 0.72 of the other kernels, 1.06 with 16).
+    if (T <= 128) {
+        if (!lines) return J >= 49152 ? 32 : 16;
+        if (f32) {
+            if (td || (J < 49152 && !(re && J >= 32768))) return 8;
+            return J >= kCvManyWalks && !light ? 8 : 16;
+        }
+        if (gae) return 8;
+        if (J < 49152) return 16;
+        return vt || re || (fwd && tr && J >= kCvWalks) ? 32 : 8;
+    }
+    // Longer ones: LC = 32, fewer and longer pieces of each row at a time (GAE float32 512 x 32768 78.3
+    // -> 62.2, 67.5 and 74.1 with LC = 16 and 8, 150 x 60001 54.5 -> 40.1; bfloat16 V-Trace 192 x 65536 56.3
+    // -> 46.5, 63.5 with 8). Narrower where its blocks are fewer than the workgroups that fit (bfloat16
+    // eligibility traces 500 x 20000 23.9 against 27.2) or one and a quarter per CU (GAE 256 x 40960 42.9
+    // against 50.0). Float32 on lines gains least: truncated TD(lambda) 160 x 100000 62.5 on walks against
+    // 73.3; GAE, V-Trace and Retrace without truncation 160 x 40960 1.01 to 1.13 of the other kernels.
+    if ((thin || (f32 && lines && !tr)) && J < (!f32 ? 36864 : T <= 192 ? 28672 : 24576)) return f32 && lines ? 8 : 16;
+    if (f32 && lines && td && tr && J >= 40000) return T <= 192 ? 0 : 16;
+    if (f32 && lines && !tr && !thin && J >= (re ? 32768 : 40000) && J < 57344) return 0;
+    return lines && T > 192 && J >= 40000 && J < 49152 ? 16 : 32;
 }
 
 template <class Op>
@@ -268,7 +345,7 @@ rlcs_status col_dispatch(Args& a, const ColGeom& g, rlcs_dtype dtype, bool has_t
                        blocks <= int64_t(UINT32_MAX) / P;
     const int forced = g_variant;
     if (forced == 0) {
-        if (const int lc = colvec_lanes(g, a.T, dtype)) {
+        if (const int lc = colvec_lanes<Op>(g, a.T, dtype, Op::kFlags && has_trunc)) {
             return colvec_launch<Op>(a, g, dtype, Op::kFlags && has_trunc, lc, reinterpret_cast<hipStream_t>(stream))
                        ? RLCS_OK : RLCS_ERR_LAUNCH;
         }

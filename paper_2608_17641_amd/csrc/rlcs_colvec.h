@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(kCvMaxWaves * kWave) cols_vec_kernel(Args a, C
 }
 
 // Launches for one policy (instantiated one translation unit per policy or two, since the kernels
-// are large): lc = 8, 16 or 32.
+// are large): lc = 4, 8, 16 or 32; 8 or 16 for vector traces.
 constexpr int kCvK = 4;  // steps per lane
 
 template <class Op>
@@ -315,7 +315,13 @@ void launch(const Args& a, const ColGeom& g, hipStream_t s) {
     constexpr int steps = kWave / LC * kCvK;  // per wave
     const int64_t blocks = (g.J + LC * kCvV - 1) / (LC * kCvV);
     const int64_t need = (a.T + steps - 1) / steps;
-    const unsigned W = unsigned(need < kCvMaxWaves ? need : kCvMaxWaves);
+    // no more waves than share the chunks evenly: 160 steps of LC = 16 in two chunks of five waves, not
+    // eight and two (V-Trace 160 x 65536 float32 64.6 -> 62.6 us, 160 x 60001 75.4 -> 68.7). Not where
+    // vector traces have three blocks or more per CU: 325 x 150 x 200 bfloat16 16.8 against 18.7 (with two,
+    // 165 x 150 x 200 12.1 -> 10.2)
+    const int64_t chunks = FCOL || blocks < 768 ? (need + kCvMaxWaves - 1) / kCvMaxWaves : 1;
+    const int64_t even = (need + chunks - 1) / chunks;
+    const unsigned W = unsigned(even < kCvMaxWaves ? even : kCvMaxWaves);
     hipLaunchKernelGGL((cols_vec_kernel<Op, DT, kCvK, LC, TR, FCOL>), dim3(unsigned(blocks)), dim3(W * kWave),
                        0, s, a, g, blocks);
 }
@@ -332,7 +338,11 @@ void launch_lc(const Args& a, const ColGeom& g, int lc, hipStream_t s) {
 template <class Op, typename DT, bool TR>
 void launch_flags(const Args& a, const ColGeom& g, int lc, hipStream_t s) {
     if constexpr (std::is_same<Op, ForwardOp<true, false>>::value) {
-        if (!g.fcol) return launch_lc<Op, DT, TR, false>(a, g, lc, s);
+        if (!g.fcol) {
+            if (lc == 8) launch<Op, DT, TR, false, 8>(a, g, s);
+            else launch<Op, DT, TR, false, 16>(a, g, s);
+            return;
+        }
     }
     launch_lc<Op, DT, TR, true>(a, g, lc, s);
 }

@@ -93,3 +93,21 @@ def test_vector_traces(N, T, F, dtype):
                                     None if tr is None else ro["trunc"][rows], gamma=0.99, lam=0.95)
         _close(z[torch.from_numpy(rows).cuda()], ref)
         assert not torch.isnan(z).any()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,T,pad", [
+    (1024, 300, 0), (1500, 80, 0), (1504, 16, 0), (8192, 128, 0), (8192, 129, 0), (8200, 513, 0), (12288, 150, 0),
+    (16384, 256, 0), (16385, 272, 0), (20000, 145, 0), (40960, 260, 0), (49152, 160, 0), (65472, 64, 0),
+    (65537, 80, 0), (65536, 97, 0), (90112, 49, 0), (90113, 80, 0)])
+def test_choice_of_blocks(N, T, pad, dtype):
+    """Both sides of the bounds between block widths and kernels, and chunks shared evenly by fewer
+    than eight waves (145, 160 and 272 steps)."""
+    test_time_major(N, T, pad, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,T,F", [(2731, 40, 12), (1639, 64, 20), (1639, 65, 20), (1366, 257, 24), (820, 257, 40), (330, 145, 200)])
+def test_vector_traces_of_few_features(N, T, F, dtype):
+    """Both sides of the bounds on features and steps from 32768 columns on."""
+    test_vector_traces(N, T, F, dtype)
